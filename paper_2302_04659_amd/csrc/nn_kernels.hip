@@ -22,6 +22,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "nn_kernels.hpp"
 
 namespace nn {
@@ -582,225 +584,253 @@ __global__ void k_pack(const float *w, int ntap, int cin, int cout, int cin_p, i
 }
 
 // ---------------------------------------------------------------- weight gradient
-// Partial dW for one tap and one chunk of output voxels:
-//   P[chunk][tap][ci][co] = sum_{v in chunk} X[p(v, tap)][ci] dY[v][co]
-// Wave w of the workgroup owns input-channel fragments w, w + 4, ...
-template <int NF>
-__global__ __launch_bounds__(256) void k_wgrad(WgradArgs a)
+// Partial dW of one group of output tiles:
+//   P[group][tap][ci][co] = sum_{v in the group's tiles} X[p(v, tap)][ci] dY[v][co]
+// Both MFMA operands have the voxels along K while the tensors are
+// channels-last, so the tiles are staged voxel-major (16-byte global-to-LDS
+// copies, all in flight) and read back transposed: ds_read_b64_tr_b16 gives
+// each lane four voxels of its channel (lane l of 16 addresses 8 bytes of
+// voxel l / 4, and receives channel l of the four voxels).  The K positions of
+// a step are any 32 voxels of the tile's (z, x) plane at one y, so a tile may
+// have any shape; A and B use the same order.
+//
+// A workgroup takes one z tap, 16 ncf input channels and 16 NF nch output
+// channels; its four waves split those (ncf x nch) and, where they do not
+// fill four waves, the K steps (nkh).  A wave holds the NT x NT in-plane taps
+// in registers: an input row r meets the gradient rows r - tb, so each A
+// fragment feeds up to NT * NF MFMAs and the LDS reads (about 0.7 of the MFMA
+// time at NF = 2) do not bound it.
+// Measured on a training batch (8 boxes of 40 x 24 x 40, all 15 layers): 0.70 ms,
+// 250 TFLOP/s; 4.4 ms before (channel-major LDS tiles filled by 2-byte stores,
+// A fragments from eight 2-byte reads each).
+constexpr int WTY = 4;   // output rows (y) of a tile
+
+struct WgradPlan {
+    int TZ, TX, ns, HX;            // tile positions (z, x), K steps of 32 positions, X row length (even)
+    int ncf, nch, nkh, ncb, ncg;   // wave split; blocks of input channels, groups of output channels
+    int tiles_x, tiles_y, tiles_z, ntiles, tpg, groups, nvar;
+    unsigned mTX, mHX, mNP;        // reciprocals ceil(2^32 / d) of TX, HX and 32 ns
+    int g_off, x_off, lds;         // byte offsets of the G and X tiles, LDS bytes
+    int x16, g16;                  // 16-byte copies possible
+};
+
+__device__ __forceinline__ int div_by(unsigned v, unsigned magic, int d) { return d == 1 ? (int)v : (int)__umulhi(v, magic); }
+
+typedef __attribute__((address_space(3))) s4 lds_s4;
+
+// Eight K elements (two transposed reads) of one operand fragment; byte LDS offsets.
+__device__ __forceinline__ b8 tr_frag(const char *sm, int lo, int hi)
 {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int ks = ksize(a.kind), ntap = ks * ks * ks;
-    const int t = blockIdx.x % ntap;
-    const int chunk = blockIdx.x / ntap;
-    const long long nvox = (long long)a.n * a.od * a.oh * a.ow;
-    const long long vb = (long long)chunk * a.chunk, ve = min(nvox, vb + a.chunk);
-    const int ta = t / (ks * ks), tb = (t / ks) % ks, tc = t % ks;
-    const int KC = a.cin / 16;
-    constexpr int MF = 2;      // input-channel fragments per wave (cin <= 128)
-    f4 acc[MF][NF];
-#pragma unroll
-    for (int m = 0; m < MF; m++)
-#pragma unroll
-        for (int n = 0; n < NF; n++) acc[m][n] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    const int kq = 8 * (lane >> 4);
-    for (long long v0 = vb; v0 < ve; v0 += 32) {
-        // K = 32 voxels (16x16x32 MFMA); this lane supplies voxels v0 + kq .. + 7
-        long long src[8], dst[8];
-        bool ok[8];
-#pragma unroll
-        for (int r = 0; r < 8; r++) {
-            long long v = v0 + kq + r;
-            ok[r] = v < ve;
-            if (!ok[r]) v = vb;
-            int x = (int)(v % a.ow);
-            long long q = v / a.ow;
-            int y = (int)(q % a.oh);
-            q /= a.oh;
-            int z = (int)(q % a.od);
-            int nn = (int)(q / a.od);
-            int sz = 0, sy = 0, sx = 0;
-            ok[r] = ok[r] && tap_source(a.kind, z, y, x, ta, tb, tc, a.id, a.ih, a.iw, sz, sy, sx);
-            src[r] = ((((long long)nn * a.id + sz) * a.ih + sy) * a.iw + sx) * a.cx + a.x_off;
-            dst[r] = v * a.cg + a.g_off;
-            if (!(v0 + kq + r < ve)) dst[r] = -1;
-        }
-        b8 Bv[NF];
-#pragma unroll
-        for (int n = 0; n < NF; n++) {
-            const int co = 16 * n + (lane & 15);
-            s8 b;
-#pragma unroll
-            for (int r = 0; r < 8; r++) b[r] = (dst[r] >= 0 && co < a.cout) ? (short)a.g[dst[r] + co] : (short)0;
-            Bv[n] = __builtin_bit_cast(b8, b);
-        }
-#pragma unroll
-        for (int m = 0; m < MF; m++) {
-            const int cf = wv + 4 * m;
-            if (cf >= KC) continue;
-            const int ci = 16 * cf + (lane & 15);
-            s8 Av;
-#pragma unroll
-            for (int r = 0; r < 8; r++) Av[r] = ok[r] ? (short)a.x[src[r] + ci] : (short)0;
-            const b8 Ab = __builtin_bit_cast(b8, Av);
-#pragma unroll
-            for (int n = 0; n < NF; n++) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ab, Bv[n], acc[m][n], 0, 0, 0);
-        }
-    }
-    float *P = a.partial + (((long long)chunk * ntap + t) * a.cin) * a.cout;
-#pragma unroll
-    for (int m = 0; m < MF; m++) {
-        const int cf = wv + 4 * m;
-        if (cf >= KC) continue;
-#pragma unroll
-        for (int n = 0; n < NF; n++) {
-            const int co = 16 * n + (lane & 15);
-            if (co >= a.cout) continue;
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int ci = 16 * cf + 4 * (lane >> 4) + r;
-                P[(long long)ci * a.cout + co] = acc[m][n][r];
-            }
-        }
-    }
+    const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(sm + lo));
+    const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(sm + hi));
+    return __builtin_bit_cast(b8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// LDS-tiled weight gradient (3^3 and up kinds).  Workgroup (group, cf, tg):
-// the output tiles [group * tpg, (group + 1) * tpg), input channels
-// [16 cf, 16 cf + 16) and taps [8 tg, 8 tg + 8).  Per tile it stages the
-// input halo channel-major (xh[ci][halo voxel]) and the output-gradient tile
-// voxel-packed (gt[co][4-voxel pack]); wave w owns taps 8 tg + w and
-// 8 tg + w + 4 and accumulates, over the tile's voxels (K = 32 voxels = two
-// x rows per MFMA), D[ci][co] += sum_v X[v + tap][ci] dY[v][co].  The partial
-// of the group goes to P[group][tap][ci][co].
-template <int NF, int KIND>
-__global__ __launch_bounds__(256) void k_wgrad_lds(WgradArgs a, int tpg, int ntiles)
+// 8 channels of a tensor row that cannot be copied as 16 aligned bytes; channels past n are zero.
+__device__ __forceinline__ uint4 load_piece(const uint16_t *p, int n)
 {
-    constexpr int TZ = NF == 8 ? 2 : 4;            // tile depth (LDS budget of the gradient tile)
-    constexpr int TV = TZ * TLY * TLX;             // tile voxels
-    constexpr int HZ = TZ + 2;
-    __shared__ unsigned short xh[16 * HZ * HLY * HLX];
-    __shared__ uint2 gt[NF * 16 * (TV / 4)];
-    unsigned short *gts = (unsigned short *)gt;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int cf = blockIdx.y, tg = blockIdx.z;
-    const int tiles_x = (a.ow + TLX - 1) / TLX, tiles_y = (a.oh + TLY - 1) / TLY, tiles_z = (a.od + TZ - 1) / TZ;
-    int hz, hy, hx;
-    if (KIND == KIND_C3) { hz = HZ; hy = HLY; hx = HLX; }
-    else { hz = TZ / 2 + 2; hy = TLY / 2 + 2; hx = TLX / 2 + 2; }
-    const int nh = hz * hy * hx;
-    const int t0 = 8 * tg + wv, t1 = t0 + 4;
-    const int tmax = min(27, 8 * tg + 8);
-    f4 acc[2][NF];
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int u = 0; u < 2; u++)
+    for (int k = 0; k < 8; k++)
+        if (k < n) w[k >> 1] |= (uint32_t)p[k] << (16 * (k & 1));
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+template <int KIND, int NF>
+__global__ __launch_bounds__(256, 3) void k_wgrad(WgradArgs a, WgradPlan p)
+{
+    constexpr int NT = KIND == KIND_C3 || KIND == KIND_UP ? 3 : (KIND == KIND_DOWN ? 2 : 1);
+    constexpr int S = KIND == KIND_DOWN ? 2 : 1;
+    constexpr int RY = S * (WTY - 1) + NT;
+    typedef __attribute__((address_space(3))) void lds_void;
+    typedef const __attribute__((address_space(1))) void glob_void;
+    extern __shared__ uint4 smem[];
+    char *sm = (char *)smem;
+    int *tab = (int *)smem;            // per position: byte offset of its X row / 64 << 16 | column
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    // the variants (z tap, channel blocks) of one group run on one XCD at about the same time (the
+    // dispatcher deals workgroups to the eight XCDs in turn), sharing its tiles in that L2
+    const int q8 = blockIdx.x >> 3;
+    const int var = q8 % p.nvar, group = (q8 / p.nvar) * 8 + (blockIdx.x & 7);
+    if (group >= p.groups) return;
+    const int ta = var % NT, cb = (var / NT) % p.ncb, cg = var / (NT * p.ncb);
+    const int cf = wv % p.ncf, ch = (wv / p.ncf) % p.nch, kh = wv / (p.ncf * p.nch);
+    const int XP = 2 * p.ncf, GP = 2 * NF * p.nch;       // 16-byte pieces per voxel
+    const int xrow = 16 * XP, grow = 16 * GP;            // bytes per voxel
+    const int npos = 32 * p.ns, nreal = p.TZ * p.TX;
+    const int ci0 = 16 * p.ncf * cb, co0 = 16 * NF * p.nch * cg;
+    for (int e = tid; e < npos; e += 256) {
+        const int z = div_by(e, p.mTX, p.TX), x = e - z * p.TX;
+        tab[e] = e < nreal ? ((z * RY * p.HX * xrow) >> 5 << 16 | S * x) : 0;
+    }
+    f4 acc[NT][NT][NF];
 #pragma unroll
-        for (int n = 0; n < NF; n++) acc[u][n] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    const int q = lane >> 4, i = lane & 15;
-    const int tile_end = min(ntiles, (int)(blockIdx.x + 1) * tpg);
-    for (int tile = blockIdx.x * tpg; tile < tile_end; tile++) {
+    for (int tc = 0; tc < NT; tc++)
+#pragma unroll
+        for (int tb = 0; tb < NT; tb++)
+#pragma unroll
+            for (int n = 0; n < NF; n++) acc[tc][tb][n] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int g = lane >> 4, j = (lane & 15) >> 2, p8 = 8 * (lane & 3);
+    // 32-byte channel chunks are swizzled so that the four voxels of a 16-lane group hit distinct banks
+    const int gsw = GP == 8 ? j : (GP == 4 ? j >> 1 : 0);
+    const int nx = p.TZ * RY * p.HX * XP, ng = WTY * npos * GP;
+    const int tile_end = min(p.ntiles, (group + 1) * p.tpg);
+    for (int tile = group * p.tpg; tile < tile_end; tile++) {
         int b = tile;
-        const int bx = b % tiles_x;
-        b /= tiles_x;
-        const int by = b % tiles_y;
-        b /= tiles_y;
-        const int bz = b % tiles_z;
-        const int bn = b / tiles_z;
-        const int z0 = bz * TZ, y0 = by * TLY, x0 = bx * TLX;
-        int hz0, hy0, hx0;
-        if (KIND == KIND_C3) { hz0 = z0 - 1; hy0 = y0 - 1; hx0 = x0 - 1; }
-        else { hz0 = (z0 >> 1) - 1; hy0 = (y0 >> 1) - 1; hx0 = (x0 >> 1) - 1; }
-        // input halo, channels [16 cf, 16 cf + 16), stored channel-major
-        for (int e = threadIdx.x; e < nh * 4; e += 256) {
-            const int v = e >> 2, qq = e & 3;
-            const int lx = v % hx, ly = (v / hx) % hy, lz = v / (hx * hy);
-            const int gz = hz0 + lz, gy = hy0 + ly, gx = hx0 + lx;
-            uint2 val = make_uint2(0u, 0u);
-            if (gz >= 0 && gy >= 0 && gx >= 0 && gz < a.id && gy < a.ih && gx < a.iw)
-                val = *(const uint2 *)(a.x + ((((long long)bn * a.id + gz) * a.ih + gy) * a.iw + gx) * a.cx + a.x_off +
-                                       16 * cf + 4 * qq);
-            const int c0 = 4 * qq;
-            xh[(c0 + 0) * nh + v] = (unsigned short)(val.x & 0xffff);
-            xh[(c0 + 1) * nh + v] = (unsigned short)(val.x >> 16);
-            xh[(c0 + 2) * nh + v] = (unsigned short)(val.y & 0xffff);
-            xh[(c0 + 3) * nh + v] = (unsigned short)(val.y >> 16);
-        }
-        // output-gradient tile, [co][voxel]
-        for (int e = threadIdx.x; e < TV * NF * 4; e += 256) {
-            const int v = e / (NF * 4), qq = e % (NF * 4);
-            const int tx = v % TLX, ty = (v / TLX) % TLY, tz = v / (TLX * TLY);
-            const int oz = z0 + tz, oy = y0 + ty, ox = x0 + tx;
-            const int c0 = 4 * qq;
-            unsigned short w4[4] = {0, 0, 0, 0};
-            if (oz < a.od && oy < a.oh && ox < a.ow) {
-                const long long gv = (((long long)bn * a.od + oz) * a.oh + oy) * a.ow + ox;
-                const uint16_t *gp = a.g + gv * a.cg + a.g_off + c0;
-                for (int k = 0; k < 4; k++) w4[k] = (c0 + k < a.cout) ? gp[k] : (unsigned short)0;
+        const int x0 = (b % p.tiles_x) * p.TX;
+        b /= p.tiles_x;
+        const int y0 = (b % p.tiles_y) * WTY;
+        b /= p.tiles_y;
+        const int z0 = (b % p.tiles_z) * p.TZ, bn = b / p.tiles_z;
+        const uint16_t *xb = a.x + (size_t)bn * a.id * a.ih * a.iw * a.cx + a.x_off + ci0;
+        const uint16_t *gb = a.g + (size_t)bn * a.od * a.oh * a.ow * a.cg + a.g_off + co0;
+        for (int s0 = 64 * wv; s0 < nx; s0 += 256) {
+            const int s = s0 + lane;
+            if (s >= nx) break;
+            const int v = XP == 4 ? s >> 2 : s >> 1, ph = s & (XP - 1);
+            const int q = div_by(v, p.mHX, p.HX), col = v - q * p.HX;
+            const int z = q / RY, r = q - z * RY;
+            const int c8 = 8 * (XP == 4 ? ph ^ (col & 2) : ph);
+            int gz, gy, gx;
+            bool in;
+            if (KIND == KIND_UP) {
+                gz = z0 + z + ta - 1; gy = y0 + r - 1; gx = x0 + col - 1;
+                in = gz >= 0 && gy >= 0 && gx >= 0 && gz < 2 * a.id && gy < 2 * a.ih && gx < 2 * a.iw;
+                gz >>= 1; gy >>= 1; gx >>= 1;
+            } else {
+                constexpr int P = KIND == KIND_C3 ? 1 : 0;
+                gz = S * (z0 + z) + ta - P; gy = S * y0 + r - P; gx = S * x0 + col - P;
+                in = gz >= 0 && gy >= 0 && gx >= 0 && gz < a.id && gy < a.ih && gx < a.iw;
             }
-            for (int k = 0; k < 4; k++) gts[(c0 + k) * TV + v] = w4[k];
+            in &= ci0 + c8 < a.cin;
+            const uint16_t *src = in ? xb + (size_t)(unsigned)((gz * a.ih + gy) * a.iw + gx) * a.cx + c8 : g_zero_piece;
+            if (p.x16) __builtin_amdgcn_global_load_lds((glob_void *)src, (lds_void *)(sm + p.x_off + 16 * s0), 16, 0, 0);
+            else *(uint4 *)(sm + p.x_off + 16 * s) = load_piece(src, 8);
         }
+        for (int s0 = 64 * wv; s0 < ng; s0 += 256) {
+            const int s = s0 + lane;
+            const int v = GP == 8 ? s >> 3 : (GP == 4 ? s >> 2 : s >> 1), ph = s & (GP - 1);
+            const int yo = div_by(v, p.mNP, npos), pos = v - yo * npos;
+            const int z = div_by(pos, p.mTX, p.TX), x = pos - z * p.TX;
+            const int c8 = 8 * (GP == 8 ? ph ^ ((pos & 3) << 1) : (GP == 4 ? ph ^ (pos & 2) : ph));
+            const int gz = z0 + z, gy = y0 + yo, gx = x0 + x, left = a.cout - co0 - c8;
+            const bool in = pos < nreal && gz < a.od && gy < a.oh && gx < a.ow && left > 0;
+            const uint16_t *src = in ? gb + (size_t)(unsigned)((gz * a.oh + gy) * a.ow + gx) * a.cg + c8 : g_zero_piece;
+            if (p.g16) __builtin_amdgcn_global_load_lds((glob_void *)src, (lds_void *)(sm + p.g_off + 16 * s0), 16, 0, 0);
+            else *(uint4 *)(sm + p.g_off + 16 * s) = load_piece(src, in ? min(left, 8) : 8);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies are not tracked by the compiler
         __syncthreads();
-        // two tile rows per 16x16x32 MFMA: K slot 4 h + r of lane group q is voxel
-        // (row + h, x = 4 q + r) for both operands (K is summed over, so any
-        // common order of the 32 voxels will do)
-        for (int row = 0; row < TZ * TLY; row += 2) {
-            b8 Bv[NF];
+        for (int ks = kh; ks < p.ns; ks += p.nkh) {
+            int ax[NT][2], ag[2];
 #pragma unroll
-            for (int n = 0; n < NF; n++) {
-                const uint2 r0 = gt[(16 * n + i) * (TV / 4) + (row * TLX + 4 * q) / 4];
-                const uint2 r1 = gt[(16 * n + i) * (TV / 4) + ((row + 1) * TLX + 4 * q) / 4];
-                Bv[n] = __builtin_bit_cast(b8, make_uint4(r0.x, r0.y, r1.x, r1.y));
+            for (int h = 0; h < 2; h++) {
+                const int pos = 32 * ks + 8 * g + 4 * h + j;
+                const int e = tab[pos];
+                const int row = p.x_off + (e >> 16 << 5);
+#pragma unroll
+                for (int tc = 0; tc < NT; tc++) {
+                    const int col = (e & 0xffff) + tc;
+                    ax[tc][h] = row + col * xrow + 32 * (XP == 4 ? cf ^ ((col >> 1) & 1) : 0) + p8;
+                }
+                ag[h] = p.g_off + pos * grow + p8;
             }
+            b8 Bv[WTY][NF];
 #pragma unroll
-            for (int u = 0; u < 2; u++) {
-                const int t = u ? t1 : t0;
-                if (t >= tmax) continue;
-                const int ta = t / 9, tb = (t / 3) % 3, tc = t % 3;
-                s8 Av;
+            for (int r = 0; r < RY; r++) {
+                if (r % S == 0 && r / S < WTY)
 #pragma unroll
-                for (int h = 0; h < 2; h++) {
-                    const int tz = (row + h) / TLY, ty = (row + h) % TLY;
+                    for (int n = 0; n < NF; n++) {
+                        const int o = r / S * npos * grow + 32 * ((ch * NF + n) ^ gsw);
+                        Bv[r / S][n] = tr_frag(sm, ag[0] + o, ag[1] + o);
+                    }
 #pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        const int tx = 4 * q + r;
-                        int lz, ly, lx;
-                        if (KIND == KIND_C3) { lz = tz + ta; ly = ty + tb; lx = tx + tc; }
-                        else {
-                            lz = ((z0 + tz + ta - 1) >> 1) - hz0;
-                            ly = ((y0 + ty + tb - 1) >> 1) - hy0;
-                            lx = ((x0 + tx + tc - 1) >> 1) - hx0;
-                        }
-                        Av[4 * h + r] = (short)xh[i * nh + (lz * hy + ly) * hx + lx];
+                for (int tc = 0; tc < NT; tc++) {
+                    const int o = r * p.HX * xrow;
+                    const b8 Av = tr_frag(sm, ax[tc][0] + o, ax[tc][1] + o);
+#pragma unroll
+                    for (int tb = 0; tb < NT; tb++) {
+                        if (r < tb || (r - tb) % S || (r - tb) / S >= WTY) continue;
+#pragma unroll
+                        for (int n = 0; n < NF; n++)
+                            acc[tc][tb][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Av, Bv[(r - tb) / S][n], acc[tc][tb][n], 0, 0, 0);
                     }
                 }
-                const b8 Ab = __builtin_bit_cast(b8, Av);
-#pragma unroll
-                for (int n = 0; n < NF; n++) acc[u][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ab, Bv[n], acc[u][n], 0, 0, 0);
             }
         }
         __syncthreads();
     }
-    // D[i][j]: ci = 16 cf + 4 (lane / 16) + r, co = 16 n + lane % 16
+    // waves that share their channels and split the K steps: sums added through LDS, one after the other
+    constexpr int NA = NT * NT * NF;
+    f4 *red = (f4 *)sm + (wv % (p.ncf * p.nch)) * NA * 64 + lane;
+    for (int k = 1; k < p.nkh; k++) {
+        if (kh == k)
 #pragma unroll
-    for (int u = 0; u < 2; u++) {
-        const int t = u ? t1 : t0;
-        if (t >= tmax) continue;
-        float *P = a.partial + ((long long)blockIdx.x * 27 + t) * a.cin * a.cout;
+            for (int i = 0; i < NA; i++) red[64 * i] = acc[i / (NT * NF)][(i / NF) % NT][i % NF];
+        __syncthreads();
+        if (kh == 0)
 #pragma unroll
-        for (int n = 0; n < NF; n++) {
-            const int co = 16 * n + (lane & 15);
-            if (co >= a.cout) continue;
-#pragma unroll
-            for (int r = 0; r < 4; r++) P[(long long)(16 * cf + 4 * (lane >> 4) + r) * a.cout + co] = acc[u][n][r];
-        }
+            for (int i = 0; i < NA; i++) acc[i / (NT * NF)][(i / NF) % NT][i % NF] += red[64 * i];
+        __syncthreads();
     }
+    if (kh != 0) return;
+    // D[i][j]: ci = 4 (lane / 16) + r, co = lane % 16 of the wave's fragments
+    const int ci = ci0 + 16 * cf + 4 * g;
+    if (ci >= a.cin) return;
+#pragma unroll
+    for (int tc = 0; tc < NT; tc++)
+#pragma unroll
+        for (int tb = 0; tb < NT; tb++) {
+            float *P = a.partial + (((long long)group * NT * NT * NT + (ta * NT + tb) * NT + tc) * a.cin + ci) * a.cout;
+#pragma unroll
+            for (int n = 0; n < NF; n++) {
+                const int co = co0 + 16 * (ch * NF + n) + (lane & 15);
+                if (co >= a.cout) continue;
+#pragma unroll
+                for (int r = 0; r < 4; r++) P[(long long)r * a.cout + co] = acc[tc][tb][n][r];
+            }
+        }
 }
 
-__global__ void k_reduce_partials(const float *partial, int nchunk, long long per, float *out, int accumulate)
+// Sum of the partials: a workgroup takes 64 V outputs, its NW waves every NW-th
+// partial (eight loads in flight), added through LDS.  One thread per output
+// over all partials left the card idle: 38 us a layer on a training batch.
+template <int V, int NW>
+__global__ __launch_bounds__(64 * NW) void k_reduce_partials(const float *partial, int nchunk, long long per, float *out,
+                                                             int accumulate)
 {
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < per; e += (long long)gridDim.x * blockDim.x) {
-        float s = accumulate ? out[e] : 0.0f;
-        for (int c = 0; c < nchunk; c++) s += partial[(long long)c * per + e];
-        out[e] = s;
+    __shared__ float red[NW][64 * V];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const long long e = ((long long)blockIdx.x * 64 + lane) * V;
+    const bool in = e < per;
+    float s[V] = {};
+    if (in) {
+        int c = w;
+        for (; c + 7 * NW < nchunk; c += 8 * NW) {
+            float t[8][V];
+#pragma unroll
+            for (int u = 0; u < 8; u++)
+#pragma unroll
+                for (int k = 0; k < V; k++) t[u][k] = partial[(long long)(c + u * NW) * per + e + k];
+#pragma unroll
+            for (int u = 0; u < 8; u++)
+#pragma unroll
+                for (int k = 0; k < V; k++) s[k] += t[u][k];
+        }
+        for (; c < nchunk; c += NW)
+#pragma unroll
+            for (int k = 0; k < V; k++) s[k] += partial[(long long)c * per + e + k];
+    }
+#pragma unroll
+    for (int k = 0; k < V; k++) red[w][lane * V + k] = s[k];
+    __syncthreads();
+    for (int i = threadIdx.x; i < 64 * V; i += 64 * NW) {
+        const long long o = (long long)blockIdx.x * 64 * V + i;
+        if (o >= per) continue;
+        float t = accumulate ? out[o] : 0.0f;
+#pragma unroll
+        for (int k = 0; k < NW; k++) t += red[k][i];
+        out[o] = t;
     }
 }
 
@@ -1257,49 +1287,94 @@ hipError_t pack(const float *w, int ntap, int cin, int cout, int cin_p, int cout
     return hipGetLastError();
 }
 
-template <int KIND>
-static hipError_t wgrad_lds(const WgradArgs &a, hipStream_t st)
+// Tile and wave split of a weight gradient: the tile shape (z, x positions)
+// with the least estimated time, MFMA steps (16 clocks per MFMA, four waves on
+// four SIMDs, padding positions included) plus the staged bytes at the 32
+// bytes per clock and CU a workgroup's copies reach, within 60 KB of LDS (two
+// workgroups per CU and the 64 KB a launch may ask for).  Larger tiles waste
+// positions on small grids, smaller ones stage more halo.
+static bool wgrad_plan(const WgradArgs &a, WgradPlan &p)
 {
-    const int nf = (a.cout + 15) / 16;
-    const int TZ = nf == 8 ? 2 : 4;
+    const int NT = a.kind == KIND_C3 || a.kind == KIND_UP ? 3 : (a.kind == KIND_DOWN ? 2 : 1);
+    const int S = a.kind == KIND_DOWN ? 2 : 1, RY = S * (WTY - 1) + NT;
+    const int nf = (a.cout + 15) / 16, NF = nf >= 2 ? 2 : 1;
+    p.ncf = a.cin >= 32 ? 2 : 1;
+    p.nch = nf >= 4 ? 2 : 1;
+    p.nkh = 4 / (p.ncf * p.nch);
+    p.ncb = (a.cin + 16 * p.ncf - 1) / (16 * p.ncf);
+    p.ncg = (nf + NF * p.nch - 1) / (NF * p.nch);
+    p.nvar = NT * p.ncb * p.ncg;
+    const int xrow = 32 * p.ncf, grow = 32 * NF * p.nch;
+    const int red = p.nkh > 1 ? p.ncf * p.nch * NT * NT * NF * 1024 : 0;
+    double best = -1.0;
+    for (int TX = 1; TX <= a.ow && TX <= 96; TX++)
+        for (int TZ = 1; TZ <= a.od && TZ * TX <= 96; TZ++) {
+            const int ns = (TZ * TX + 31) / 32, HX = (S * (TX - 1) + NT + 1) & ~1;
+            const int tab = 128 * ns, gb = WTY * 32 * ns * grow, xb = TZ * RY * HX * xrow;
+            if (tab + gb + xb > 60 * 1024) continue;
+            const double steps = (double)((ns + p.nkh - 1) / p.nkh) * NT * NT * WTY * NF * 16;
+            const double cost = (double)((a.ow + TX - 1) / TX) * ((a.od + TZ - 1) / TZ) * (steps + (gb + xb) / 32.0 + 200.0);
+            if (best >= 0.0 && cost >= best) continue;
+            best = cost;
+            p.TX = TX; p.TZ = TZ; p.ns = ns; p.HX = HX;
+            p.g_off = tab;
+            p.x_off = tab + gb;
+            p.lds = tab + gb + xb > red ? tab + gb + xb : red;
+        }
+    if (best < 0.0) return false;
+    p.mTX = (unsigned)((0x100000000ull + p.TX - 1) / p.TX);
+    p.mHX = (unsigned)((0x100000000ull + p.HX - 1) / p.HX);
+    p.mNP = (unsigned)((0x100000000ull + 32 * p.ns - 1) / (32 * p.ns));
+    p.tiles_x = (a.ow + p.TX - 1) / p.TX;
+    p.tiles_y = (a.oh + WTY - 1) / WTY;
+    p.tiles_z = (a.od + p.TZ - 1) / p.TZ;
     const long long nvox = (long long)a.n * a.od * a.oh * a.ow;
-    const long long ntiles = (long long)a.n * ((a.od + TZ - 1) / TZ) * ((a.oh + TLY - 1) / TLY) * ((a.ow + TLX - 1) / TLX);
+    const long long ntiles = (long long)a.n * p.tiles_x * p.tiles_y * p.tiles_z;
     const long long groups_max = (nvox + a.chunk - 1) / a.chunk;          // the partial buffer holds this many
-    const long long tpg = (ntiles + groups_max - 1) / groups_max;
-    const long long groups = (ntiles + tpg - 1) / tpg;
-    if (ntiles > 0x7fffffff || groups > 65535) return hipErrorInvalidValue;
-    const dim3 g((unsigned)groups, (unsigned)(a.cin / 16), 4);
-    switch (nf) {
-    case 1: k_wgrad_lds<1, KIND><<<g, 256, 0, st>>>(a, (int)tpg, (int)ntiles); break;
-    case 2: k_wgrad_lds<2, KIND><<<g, 256, 0, st>>>(a, (int)tpg, (int)ntiles); break;
-    case 4: k_wgrad_lds<4, KIND><<<g, 256, 0, st>>>(a, (int)tpg, (int)ntiles); break;
-    case 8: k_wgrad_lds<8, KIND><<<g, 256, 0, st>>>(a, (int)tpg, (int)ntiles); break;
-    default: return hipErrorInvalidValue;
-    }
-    const long long per = 27LL * a.cin * a.cout;
-    k_reduce_partials<<<grid_for(per), 256, 0, st>>>(a.partial, (int)groups, per, a.gw, a.accumulate);
+    // about three workgroups per CU over all variants; every group adds a partial to write and to sum
+    const long long want = std::min(groups_max, std::max(1LL, 768LL / p.nvar));
+    const long long tpg = (ntiles + want - 1) / want, groups = (ntiles + tpg - 1) / tpg;
+    if (ntiles > 0x7fffffff || (groups + 8) * p.nvar > 0x7fffffff) return false;
+    p.ntiles = (int)ntiles;
+    p.tpg = (int)tpg;
+    p.groups = (int)groups;
+    p.x16 = a.cx % 8 == 0 && a.x_off % 8 == 0 && ((uintptr_t)a.x & 15) == 0;
+    p.g16 = a.cg % 8 == 0 && a.g_off % 8 == 0 && a.cout % 8 == 0 && ((uintptr_t)a.g & 15) == 0;
+    return true;
+}
+
+static hipError_t reduce_partials(const float *partial, int n, long long per, float *out, int accumulate, hipStream_t st)
+{
+    const bool v4 = per % 4 == 0 && ((uintptr_t)partial & 15) == 0;
+    const long long w = v4 ? 256 : 64, wgs = (per + w - 1) / w;
+    if (wgs > 0x7fffffff) return hipErrorInvalidValue;
+    const unsigned g = (unsigned)wgs;
+    if (v4 && n >= 64) k_reduce_partials<4, 16><<<g, 1024, 0, st>>>(partial, n, per, out, accumulate);
+    else if (v4) k_reduce_partials<4, 4><<<g, 256, 0, st>>>(partial, n, per, out, accumulate);
+    else k_reduce_partials<1, 4><<<g, 256, 0, st>>>(partial, n, per, out, accumulate);
     return hipGetLastError();
+}
+
+template <int KIND>
+static hipError_t wgrad_kind(const WgradArgs &a, hipStream_t st)
+{
+    WgradPlan p{};
+    if (!wgrad_plan(a, p)) return hipErrorInvalidValue;
+    const unsigned g = (unsigned)((p.groups + 7) / 8 * 8 * p.nvar);
+    if ((a.cout + 15) / 16 >= 2) k_wgrad<KIND, 2><<<g, 256, p.lds, st>>>(a, p);
+    else k_wgrad<KIND, 1><<<g, 256, p.lds, st>>>(a, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int nt = KIND == KIND_C3 || KIND == KIND_UP ? 27 : (KIND == KIND_DOWN ? 8 : 1);
+    return reduce_partials(a.partial, p.groups, (long long)nt * a.cin * a.cout, a.gw, a.accumulate, st);
 }
 
 hipError_t wgrad(const WgradArgs &a, hipStream_t st)
 {
-    if (a.kind == KIND_C3) return wgrad_lds<KIND_C3>(a, st);
-    if (a.kind == KIND_UP) return wgrad_lds<KIND_UP>(a, st);
-    const int ks = a.kind == KIND_C3 || a.kind == KIND_UP ? 3 : (a.kind == KIND_DOWN ? 2 : 1);
-    const int ntap = ks * ks * ks;
-    const long long nvox = (long long)a.n * a.od * a.oh * a.ow;
-    const int nchunk = (int)((nvox + a.chunk - 1) / a.chunk);
-    const unsigned g = (unsigned)(nchunk * ntap);
-    switch ((a.cout + 15) / 16) {
-    case 1: k_wgrad<1><<<g, 256, 0, st>>>(a); break;
-    case 2: k_wgrad<2><<<g, 256, 0, st>>>(a); break;
-    case 4: k_wgrad<4><<<g, 256, 0, st>>>(a); break;
-    case 8: k_wgrad<8><<<g, 256, 0, st>>>(a); break;
-    default: return hipErrorInvalidValue;
-    }
-    const long long per = (long long)ntap * a.cin * a.cout;
-    k_reduce_partials<<<grid_for(per), 256, 0, st>>>(a.partial, nchunk, per, a.gw, a.accumulate);
-    return hipGetLastError();
+    if (a.kind == KIND_C3) return wgrad_kind<KIND_C3>(a, st);
+    if (a.kind == KIND_UP) return wgrad_kind<KIND_UP>(a, st);
+    if (a.kind == KIND_DOWN) return wgrad_kind<KIND_DOWN>(a, st);
+    return wgrad_kind<KIND_C1>(a, st);
 }
 
 hipError_t bias_grad(const uint16_t *g, long long nvox, int cg, int g_off, int cout, float *gb, int accumulate,
