@@ -23,6 +23,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "nn_kernels.hpp"
 
@@ -38,6 +39,13 @@ __device__ __forceinline__ uint16_t f2bf(float f)
     if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffff) ? 0x40 : 0));   // inf / nan
     u += 0x7fffu + ((u >> 16) & 1u);                                                                 // nearest even
     return (uint16_t)(u >> 16);
+}
+
+// Two of them packed (v_cvt_pk_bf16_f32 rounds to nearest even and keeps infinities and NaN).
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi)
+{
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, b2{(__bf16)lo, (__bf16)hi});
 }
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
@@ -340,131 +348,189 @@ __device__ __forceinline__ void conv_store(const ConvArgs &a, f4 (&acc)[FR][NF],
     }
 }
 
-// The same tiling on v_mfma_f32_16x16x32_bf16 for a multiple of 32 input
-// channels.  K slot e of lane group g (= lane / 16) carries channel 8 g + e of
-// the 32-channel chunk, for A (halo) and B (packed weights) alike.  The halo
-// holds, per voxel, the chunk's four 16-byte pieces (channels 8 p .. 8 p + 7),
-// piece p stored at slot p ^ ((v >> 2) & 3) so that the 16-byte reads of 8
-// neighbouring x voxels hit distinct banks.  For each (z tap, x tap) a wave
-// reads the six halo rows its four output rows see through the three y taps
-// once.  With 16-byte aligned channel slices (x16) the halo is staged by
-// 16-byte global-to-LDS copies (global_load_lds_dwordx4): each wave
-// instruction fills 64 consecutive slots, lane L slot 64 j + L, so every load
-// of a chunk is in flight at once and no register holds the data; voxels in
-// the padding copy from a zero block.  A BF16 output slice goes out through
-// LDS as 16-byte rows (needs the channel stride and offset of x and y to be
-// multiples of 8).
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 
 __device__ __align__(16) uint16_t g_zero_piece[8];   // 16 zero bytes: the source of padding voxels
 
-// FR: output rows (y) per wave, 4 or 8 (tile 4 x FR x 16).  Every B fragment
-// (weights, read through the vector cache) feeds FR MFMAs; at FR = 4 those
-// reads alone would use the cache's whole bandwidth at the MFMA rate (a
-// timing-only build that skips them runs the forward 1.4x faster).
-template <int NF, int KIND, bool X16, int FR>
-__global__ __launch_bounds__(256, 2) void k_conv_lds32(ConvArgs a)
+// floor(v / d) by the reciprocal ceil(2^32 / d), v < 2^16.
+__device__ __forceinline__ int div_by(unsigned v, unsigned magic, int d) { return d == 1 ? (int)v : (int)__umulhi(v, magic); }
+
+// 8 channels of a tensor row that cannot be copied as 16 aligned bytes; channels past n are zero.
+__device__ __forceinline__ uint4 load_piece(const uint16_t *p, int n)
 {
-    constexpr int HZ = KIND == KIND_C3 ? HLZ : TLZ / 2 + 2;
-    constexpr int HY = KIND == KIND_C3 ? FR + 2 : FR / 2 + 2;
-    constexpr int HX = KIND == KIND_C3 ? HLX : TLX / 2 + 2;
-    constexpr int NH = HZ * HY * HX;
-    constexpr int HBUF = HLZ * (FR + 2) * HLX * 4;   // uint4 slots of the largest (3^3) halo
-    static_assert(64 * FR * (store_pass_channels<NF, FR>() + 8) * 2 <= HBUF * 16, "output rows must fit the halo buffer");
-    __shared__ uint4 halo[HBUF];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int tiles_x = (a.ow + TLX - 1) / TLX, tiles_y = (a.oh + FR - 1) / FR, tiles_z = (a.od + TLZ - 1) / TLZ;
-    int b = blockIdx.x;
-    const int bx = b % tiles_x;
-    b /= tiles_x;
-    const int by = b % tiles_y;
-    b /= tiles_y;
-    const int bz = b % tiles_z;
-    const int bn = b / tiles_z;
-    const int z0 = bz * TLZ, y0 = by * FR, x0 = bx * TLX;
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int k = 0; k < 8; k++)
+        if (k < n) w[k >> 1] |= (uint32_t)p[k] << (16 * (k & 1));
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// 3^3 and upsampling convolution on v_mfma_f32_16x16x32_bf16 for a multiple of
+// 32 input channels.  K slot e of lane group g (= lane / 16) carries channel
+// 8 g + e of the 32-channel chunk, for A (halo) and B (packed weights) alike.
+//
+// A workgroup computes a tile of TZ x FR x TX (z, y, x) output voxels.  The 16
+// rows of an A fragment are any 16 positions of the tile's (z, x) plane at one
+// y (each lane keeps the halo offsets of its position), so a tile can be cut
+// to the grid instead of to 4 x 16: on the 40 x 24 x 40, 20 x 12 x 20 and
+// 10 x 6 x 10 levels of a 40 x 24 x 40 box 4 x 4 x 16 tiles spend 17, 37 and
+// 61 % of the MFMAs on padding.  Wave (pw, cw) owns positions 16 pw .. + 15,
+// all FR rows and output channels 16 NF (cw + ...) .. + 16 NF - 1.  For each
+// (z tap, x tap) it reads the FR + 2 halo rows its FR output rows see through
+// the three y taps once; every B fragment (weights, through the vector cache)
+// feeds FR MFMAs, so that at FR = 8 and NF = 2 neither the LDS (53 of 128
+// bytes per clock at the MFMA rate) nor the vector cache (31 of 64) bounds it.
+// The halo holds, per voxel, the chunk's four 16-byte pieces (channels
+// 8 p .. 8 p + 7), piece p at slot p ^ ((x >> 2) & 3) so that the reads of 8
+// neighbouring voxels hit distinct banks.  It is staged by 16-byte
+// global-to-LDS copies, every load of a chunk in flight at once; voxels in the
+// padding copy from a zero block.  The weights are the MFMA's row operand, so
+// that a lane ends with four consecutive channels of one voxel and stores
+// them as 8 bytes (through LDS, as 16-byte rows, the epilogue took a third of
+// a 32 -> 32 layer).  The order of the sum (channel chunk, z tap, x tap,
+// y tap) does not depend on the tile.  Measured on 64 boxes of 40 x 24 x 40
+// (us, 4 x 4 or 4 x 8 x 16 tiles before): 32 -> 32 141 (235), 64 -> 32 262 (430),
+// 64 -> 64 at half size 61 (147), 128 -> 128 at quarter size 37 (190),
+// upsampling 64 -> 32 167 (314) and 128 -> 64 98 (231).
+struct ConvPlan {
+    int TZ, TX, PW, CW;            // tile positions, waves along positions and output channels
+    int HZ, HY, HX;                // halo extents
+    int tiles_x, tiles_y, tiles_z, ntiles, nco;
+    unsigned mTX, mHX, mHY;        // reciprocals ceil(2^32 / d)
+    int x16, lds;
+};
+
+template <int NF, int KIND, int FR>
+__global__ __launch_bounds__((NF == 2 && FR == 8 ? 8 : 16) * 64) void k_conv_pos(ConvArgs a, ConvPlan p)
+{
+    typedef __attribute__((address_space(3))) void lds_void;
+    typedef const __attribute__((address_space(1))) void glob_void;
+    extern __shared__ uint4 halo[];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nt = 64 * p.PW * p.CW;
+    // every XCD takes a run of neighbouring tiles (their halos overlap in its L2), and the
+    // output-channel blocks of one tile run on one XCD at about the same time
+    const int q8 = blockIdx.x >> 3;
+    const int per = (p.ntiles + 7) >> 3;
+    const int tile = (blockIdx.x & 7) * per + q8 / p.nco;
+    if (q8 / p.nco >= per || tile >= p.ntiles) return;
+    const int pw = wv % p.PW, cn = (q8 % p.nco * p.CW + wv / p.PW) * NF;   // first output fragment
+    int b = tile;
+    const int x0 = (b % p.tiles_x) * p.TX;
+    b /= p.tiles_x;
+    const int y0 = (b % p.tiles_y) * FR;
+    b /= p.tiles_y;
+    const int z0 = (b % p.tiles_z) * p.TZ, bn = b / p.tiles_z;
     int hz0, hy0, hx0;
     if (KIND == KIND_C3) {
         hz0 = z0 - 1; hy0 = y0 - 1; hx0 = x0 - 1;
-    } else {
-        hz0 = (z0 >> 1) - 1; hy0 = (y0 >> 1) - 1; hx0 = (x0 >> 1) - 1;
+    } else {   // nearest x2 upsampled input: fine u = o + t - 1 reads coarse u >> 1
+        hz0 = (z0 - 1) >> 1; hy0 = (y0 - 1) >> 1; hx0 = (x0 - 1) >> 1;
+    }
+    const int g = lane >> 4, i = lane & 15;
+    const int pos = 16 * pw + i, nreal = p.TZ * p.TX;
+    const int pz = pos < nreal ? div_by(pos, p.mTX, p.TX) : 0, px = pos < nreal ? pos - pz * p.TX : 0;
+    const int hrow = 64 * p.HX;                           // bytes of a halo row
+    int zo[3], xo[3];                                     // halo byte offsets of this lane per z and x tap
+#pragma unroll
+    for (int t = 0; t < 3; t++) {
+        zo[t] = (KIND == KIND_C3 ? pz + t : ((z0 + pz + t - 1) >> 1) - hz0) * p.HY * hrow;
+        const int lx = KIND == KIND_C3 ? px + t : ((x0 + px + t - 1) >> 1) - hx0;
+        xo[t] = 64 * lx + 16 * (g ^ ((lx >> 2) & 3));
     }
     f4 acc[FR][NF];
 #pragma unroll
     for (int f = 0; f < FR; f++)
 #pragma unroll
         for (int n = 0; n < NF; n++) acc[f][n] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    const int kc = a.cin / 32;
-    const int g = lane >> 4, i = lane & 15;
-    uint2 *h2 = (uint2 *)halo;
-    const uint16_t *xb = a.x + (long long)bn * a.id * a.ih * a.iw * a.cx + a.x_off;
+    const int kc = a.cin / 32, nft = (a.cout + 15) / 16, ns = 4 * p.HZ * p.HY * p.HX;
+    const uint16_t *xb = a.x + (size_t)bn * a.id * a.ih * a.iw * a.cx + a.x_off;
     for (int c = 0; c < kc; c++) {
-        if (X16) {
-            typedef __attribute__((address_space(3))) void lds_void;
-            typedef const __attribute__((address_space(1))) void glob_void;
-            for (int j = wv; j * 64 < 4 * NH; j += 4) {
-                const int slot = 64 * j + lane;
-                if (slot < 4 * NH) {
-                    const int v = slot >> 2, p = (slot & 3) ^ ((v >> 2) & 3);
-                    const int lx = v % HX, ly = (v / HX) % HY, lz = v / (HX * HY);
-                    const int gz = hz0 + lz, gy = hy0 + ly, gx = hx0 + lx;
-                    const bool in = gz >= 0 && gy >= 0 && gx >= 0 && gz < a.id && gy < a.ih && gx < a.iw;
-                    const uint16_t *src =
-                        in ? xb + (((long long)gz * a.ih + gy) * a.iw + gx) * a.cx + 32 * c + 8 * p : g_zero_piece;
-                    __builtin_amdgcn_global_load_lds((glob_void *)src, (lds_void *)(halo + 64 * j), 16, 0, 0);
-                }
-            }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies are not tracked by the compiler
-        } else {
-            // 4 channels per load, thread t: channels 4 (t & 7) .. + 3 of voxels (t >> 3) + 32 k
-            const int q = threadIdx.x & 7;
-            for (int v = threadIdx.x >> 3; v < NH; v += 32) {
-                const int lx = v % HX, ly = (v / HX) % HY, lz = v / (HX * HY);
-                const int gz = hz0 + lz, gy = hy0 + ly, gx = hx0 + lx;
-                const bool in = gz >= 0 && gy >= 0 && gx >= 0 && gz < a.id && gy < a.ih && gx < a.iw;
-                const long long off = (((long long)gz * a.ih + gy) * a.iw + gx) * a.cx + 32 * c + 4 * q;
-                uint2 val = make_uint2(0u, 0u);
-                if (in) val = *(const uint2 *)(xb + off);
-                h2[v * 8 + 2 * ((q >> 1) ^ ((v >> 2) & 3)) + (q & 1)] = val;
-            }
+        for (int s0 = 64 * wv; s0 < ns; s0 += nt) {
+            const int s = s0 + lane;
+            if (s >= ns) break;
+            const int v = s >> 2;
+            const int q = div_by(v, p.mHX, p.HX), lx = v - q * p.HX, lz = div_by(q, p.mHY, p.HY), ly = q - lz * p.HY;
+            const int c8 = 8 * ((s & 3) ^ ((lx >> 2) & 3));
+            const int gz = hz0 + lz, gy = hy0 + ly, gx = hx0 + lx;
+            const bool in = gz >= 0 && gy >= 0 && gx >= 0 && gz < a.id && gy < a.ih && gx < a.iw;
+            const uint16_t *src =
+                in ? xb + (size_t)(unsigned)((gz * a.ih + gy) * a.iw + gx) * a.cx + 32 * c + c8 : g_zero_piece;
+            if (p.x16) __builtin_amdgcn_global_load_lds((glob_void *)src, (lds_void *)(halo + s0), 16, 0, 0);
+            else halo[s] = load_piece(src, 8);
         }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies are not tracked by the compiler
         __syncthreads();
-        const uint16_t *wc = a.w + (size_t)c * NF * 512 + 8 * lane;
+        const uint16_t *wc = a.w + ((size_t)c * nft + cn) * 512 + 8 * lane;
+        const size_t wt = (size_t)kc * nft * 512;          // from one tap to the next
 #pragma unroll 1
         for (int ta = 0; ta < 3; ta++) {
-            int lz;
-            if (KIND == KIND_C3) lz = wv + ta;
-            else lz = ((z0 + wv + ta - 1) >> 1) - hz0;
 #pragma unroll 1
             for (int tc = 0; tc < 3; tc++) {
-                int lx;
-                if (KIND == KIND_C3) lx = i + tc;
-                else lx = ((x0 + i + tc - 1) >> 1) - hx0;
+                const int v0 = (ta == 0 ? zo[0] : (ta == 1 ? zo[1] : zo[2])) + (tc == 0 ? xo[0] : (tc == 1 ? xo[1] : xo[2]));
+                const uint16_t *w = wc + (ta * 9 + tc) * wt;
+                b8 Bv[3][NF];
+#pragma unroll
+                for (int tb = 0; tb < 3; tb++)
+#pragma unroll
+                    for (int n = 0; n < NF; n++) Bv[tb][n] = __builtin_bit_cast(b8, *(const uint4 *)(w + 3 * tb * wt + n * 512));
                 b8 Ar[FR + 2];
 #pragma unroll
                 for (int r = 0; r < FR + 2; r++) {
-                    int ly;
-                    if (KIND == KIND_C3) ly = r;
-                    else ly = ((y0 + r - 1) >> 1) - hy0;
-                    const int v = (lz * HY + ly) * HX + lx;
-                    Ar[r] = __builtin_bit_cast(b8, halo[v * 4 + (g ^ ((v >> 2) & 3))]);
+                    const int ly = KIND == KIND_C3 ? r : (r + 1) >> 1;   // y0 is even
+                    Ar[r] = __builtin_bit_cast(b8, *(const uint4 *)((const char *)halo + (v0 + ly * hrow)));
                 }
 #pragma unroll
-                for (int tb = 0; tb < 3; tb++) {
-                    const int t = (ta * 3 + tb) * 3 + tc;
-                    const uint16_t *wt = wc + (size_t)t * kc * NF * 512;
+                for (int tb = 0; tb < 3; tb++)
 #pragma unroll
-                    for (int n = 0; n < NF; n++) {
-                        const b8 Bv = __builtin_bit_cast(b8, *(const uint4 *)(wt + (size_t)n * 512));
+                    for (int n = 0; n < NF; n++)
 #pragma unroll
                         for (int f = 0; f < FR; f++)
-                            acc[f][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ar[f + tb], Bv, acc[f][n], 0, 0, 0);
-                    }
-                }
+                            acc[f][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Bv[tb][n], Ar[f + tb], acc[f][n], 0, 0, 0);
             }
         }
         __syncthreads();
     }
-    conv_store<NF, FR>(a, acc, bn, z0, y0, x0, wv, lane, (uint16_t *)halo);
+    // D[row][col]: channel 16 (cn + n) + 4 g + r of position i
+    const int gz = z0 + pz, gx = x0 + px;
+    if (pos >= nreal || gz >= a.od || gx >= a.ow) return;
+    float bias[NF][4];
+#pragma unroll
+    for (int n = 0; n < NF; n++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int co = 16 * (cn + n) + 4 * g + r;
+            bias[n][r] = a.bias && co < a.cout ? a.bias[co] : 0.0f;
+        }
+    const bool y8 = a.cy % 4 == 0 && a.y_off % 4 == 0 && ((uintptr_t)a.y & 7) == 0;   // 8-byte stores
+#pragma unroll
+    for (int f = 0; f < FR; f++) {
+        if (y0 + f >= a.oh) break;
+        const long long v = (((long long)bn * a.od + gz) * a.oh + y0 + f) * a.ow + gx;
+#pragma unroll
+        for (int n = 0; n < NF; n++) {
+            const int co = 16 * (cn + n) + 4 * g;
+            float val[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                val[r] = acc[f][n][r] + bias[n][r];
+                if (a.relu) val[r] = fmaxf(val[r], 0.0f);
+            }
+            if (a.y) {
+                uint16_t *yp = a.y + v * a.cy + a.y_off + co;
+                if (y8 && co + 4 <= a.cout) {
+                    *(uint2 *)yp = make_uint2(f2bf2(val[0], val[1]), f2bf2(val[2], val[3]));
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; r++)
+                        if (co + r < a.cout) yp[r] = f2bf(val[r]);
+                }
+            }
+            if (a.y32)
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+                    if (co + r < a.cout) a.y32[v * a.cy32 + co + r] = val[r];
+        }
+    }
 }
 
 // First layer: 3^3 convolution over 8 input channels with the taps folded
@@ -614,8 +680,6 @@ struct WgradPlan {
     int x16, g16;                  // 16-byte copies possible
 };
 
-__device__ __forceinline__ int div_by(unsigned v, unsigned magic, int d) { return d == 1 ? (int)v : (int)__umulhi(v, magic); }
-
 typedef __attribute__((address_space(3))) s4 lds_s4;
 
 // Eight K elements (two transposed reads) of one operand fragment; byte LDS offsets.
@@ -624,16 +688,6 @@ __device__ __forceinline__ b8 tr_frag(const char *sm, int lo, int hi)
     const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(sm + lo));
     const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(sm + hi));
     return __builtin_bit_cast(b8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-// 8 channels of a tensor row that cannot be copied as 16 aligned bytes; channels past n are zero.
-__device__ __forceinline__ uint4 load_piece(const uint16_t *p, int n)
-{
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int k = 0; k < 8; k++)
-        if (k < n) w[k >> 1] |= (uint32_t)p[k] << (16 * (k & 1));
-    return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 template <int KIND, int NF>
@@ -1210,34 +1264,107 @@ static unsigned grid_for(long long n, int per = 256)
     return (unsigned)(b < 16384 ? (b < 1 ? 1 : b) : 16384);
 }
 
+// Sizes of a tile along an axis of n worth looking at: n cut into 1, 2, 3, ... even parts.
+static int next_cut(int n, int t)   // the next smaller one, 0 at the end
+{
+    if (t <= 1) return 0;
+    const int k = (n + t - 1) / t;
+    for (int m = k + 1;; m++) {
+        const int u = (n + m - 1) / m;
+        if (u < t) return u;
+    }
+}
+
+static unsigned recip(int d) { return (unsigned)((0x100000000ull + d - 1) / d); }
+
+// Tile, rows per wave and wave split of a convolution with the least estimated
+// time, in clocks: a compute unit's share of the workgroups times the sum of
+// their MFMAs (20 clocks each on the four SIMDs, 16 at the peak, times the
+// busiest SIMD's share of the waves), halo bytes (10 a clock) and output bytes
+// (20 a clock), 15 % more with fewer than three workgroups per CU to overlap
+// these phases; or, where few workgroups are in flight, the rounds of one
+// workgroup's own chain (900 clocks of latency per (z, x) tap, 4,500 per
+// chunk).  Fitted to a sweep of 1,500 tiles over ten layers (32 to 128
+// channels, 8 and 64 boxes of 40 x 24 x 40 and their two coarser levels): the
+// tiles it picks are within 9 % of the fastest of each.
+static bool conv_plan(const ConvArgs &a, int NF, ConvPlan &p, int &FR)
+{
+    const bool up = a.kind == KIND_UP;
+    const int kc = a.cin / 32, groups = (a.cout + 16 * NF - 1) / (16 * NF);
+    double best = -1.0;
+    for (int fr : {8, 6, 4}) {
+        const int HY = up ? fr / 2 + 2 : fr + 2;
+        for (int TX = a.ow; TX > 0; TX = next_cut(a.ow, TX))
+            for (int TZ = a.od; TZ > 0; TZ = next_cut(a.od, TZ)) {
+                if (TX > 128 || TZ * TX > 128) continue;
+                const int PW = (TZ * TX + 15) / 16;
+                const int HX = up ? TX / 2 + 2 : TX + 2, HZ = up ? TZ / 2 + 2 : TZ + 2;
+                const int hb = 64 * HZ * HY * HX;
+                const double tiles = (double)a.n * ((a.ow + TX - 1) / TX) * ((a.oh + fr - 1) / fr) * ((a.od + TZ - 1) / TZ);
+                for (int CW = groups; CW >= 1; CW /= 2) {
+                    const int most = NF == 2 && fr == 8 ? 8 : 16;   // waves, as the launch bounds
+                    if (PW * CW > most) continue;
+                    const int lds = hb;
+                    if (lds > 80 * 1024) continue;                    // two workgroups per CU
+                    const int occ = std::min(160 * 1024 / lds, std::max(1, (most == 8 ? 12 : 16) / (PW * CW)));
+                    const double wgs = tiles * (groups / CW);
+                    const int W = PW * CW;
+                    const double mf = 27.0 * fr * NF * ((occ * W + 3) / 4) / occ, out = 16.0 * W * fr * 32 * NF;
+                    const double all = (kc * (20 * mf + hb / 10.0) + out / 20) * (occ < 3 ? 1.15 : 1.0);
+                    const double own = kc * (9 * (900.0 + 48 * fr * NF * ((W + 3) / 4)) + hb / 10.0 + 4500.0) + 2000.0;
+                    const double cost = std::max(std::ceil(wgs / 256) * all, std::ceil(wgs / (256.0 * occ)) * own);
+                    if (best >= 0.0 && cost >= best) continue;
+                    best = cost;
+                    FR = fr;
+                    p.TZ = TZ; p.TX = TX; p.PW = PW; p.CW = CW;
+                    p.HZ = HZ; p.HY = HY; p.HX = HX;
+                    p.lds = lds;
+                    p.nco = groups / CW;
+                }
+            }
+    }
+    if (best < 0.0) return false;
+    p.tiles_x = (a.ow + p.TX - 1) / p.TX;
+    p.tiles_y = (a.oh + FR - 1) / FR;
+    p.tiles_z = (a.od + p.TZ - 1) / p.TZ;
+    const long long nt = (long long)a.n * p.tiles_x * p.tiles_y * p.tiles_z;
+    if ((nt + 7) * p.nco > 0x7fffffff) return false;
+    p.ntiles = (int)nt;
+    p.mTX = recip(p.TX);
+    p.mHX = recip(p.HX);
+    p.mHY = recip(p.HY);
+    p.x16 = a.cx % 8 == 0 && a.x_off % 8 == 0 && ((uintptr_t)a.x & 15) == 0;
+    return true;
+}
+
+template <int NF, int KIND>
+static hipError_t conv_pos(const ConvArgs &a, hipStream_t st)
+{
+    ConvPlan p{};
+    int FR = 0;
+    if (!conv_plan(a, NF, p, FR)) return hipErrorInvalidValue;
+    const unsigned g = (unsigned)((p.ntiles + 7) / 8 * 8 * p.nco), t = 64 * p.PW * p.CW;
+    const void *fn = FR == 8 ? (const void *)k_conv_pos<NF, KIND, 8> : (FR == 6 ? (const void *)k_conv_pos<NF, KIND, 6> : (const void *)k_conv_pos<NF, KIND, 4>);
+    ConvArgs args = a;
+    void *params[] = {&args, &p};
+    return hipLaunchKernel(fn, dim3(g), dim3(t), params, p.lds, st);
+}
+
 template <int KIND>
 static hipError_t conv_lds(const ConvArgs &a, hipStream_t st)
 {
+    const int nf = (a.cout + 15) / 16;
+    if (nf != 1 && nf != 2 && nf != 4 && nf != 8) return hipErrorInvalidValue;
+    if (a.cin % 32 == 0)   // the weights were packed as 16x16x32 fragments (same condition in pack)
+        return nf == 1 ? conv_pos<1, KIND>(a, st) : conv_pos<2, KIND>(a, st);
     const long long tiles = (long long)a.n * ((a.od + TLZ - 1) / TLZ) * ((a.oh + TLY - 1) / TLY) * ((a.ow + TLX - 1) / TLX);
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     const unsigned g = (unsigned)tiles;
-    if (a.cin % 32 == 0) {   // the weights were packed as 16x16x32 fragments (same condition in pack)
-        const bool x16 = a.cx % 8 == 0 && a.x_off % 8 == 0 && ((uintptr_t)a.x & 15) == 0;
-        // 8 output rows per wave up to 32 output channels (measured on the 40 x 24 x 40 boxes: the
-        // forward 10.1 -> 9.8 ms; 8 rows at 64 channels cost an occupancy step and ran slower)
-        const long long t8 = (long long)a.n * ((a.od + TLZ - 1) / TLZ) * ((a.oh + 7) / 8) * ((a.ow + TLX - 1) / TLX);
-        if (t8 > 0x7fffffff) return hipErrorInvalidValue;
-        const unsigned g8 = (unsigned)t8;
-        switch ((a.cout + 15) / 16) {
-        case 1: if (x16) k_conv_lds32<1, KIND, true, 8><<<g8, 256, 0, st>>>(a); else k_conv_lds32<1, KIND, false, 8><<<g8, 256, 0, st>>>(a); break;
-        case 2: if (x16) k_conv_lds32<2, KIND, true, 8><<<g8, 256, 0, st>>>(a); else k_conv_lds32<2, KIND, false, 8><<<g8, 256, 0, st>>>(a); break;
-        case 4: if (x16) k_conv_lds32<4, KIND, true, 4><<<g, 256, 0, st>>>(a); else k_conv_lds32<4, KIND, false, 4><<<g, 256, 0, st>>>(a); break;
-        case 8: if (x16) k_conv_lds32<8, KIND, true, 4><<<g, 256, 0, st>>>(a); else k_conv_lds32<8, KIND, false, 4><<<g, 256, 0, st>>>(a); break;
-        default: return hipErrorInvalidValue;
-        }
-        return hipGetLastError();
-    }
-    switch ((a.cout + 15) / 16) {
+    switch (nf) {
     case 1: k_conv_lds<1, KIND><<<g, 256, 0, st>>>(a); break;
     case 2: k_conv_lds<2, KIND><<<g, 256, 0, st>>>(a); break;
     case 4: k_conv_lds<4, KIND><<<g, 256, 0, st>>>(a); break;
     case 8: k_conv_lds<8, KIND><<<g, 256, 0, st>>>(a); break;
-    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
@@ -1307,8 +1434,9 @@ static bool wgrad_plan(const WgradArgs &a, WgradPlan &p)
     const int xrow = 32 * p.ncf, grow = 32 * NF * p.nch;
     const int red = p.nkh > 1 ? p.ncf * p.nch * NT * NT * NF * 1024 : 0;
     double best = -1.0;
-    for (int TX = 1; TX <= a.ow && TX <= 96; TX++)
-        for (int TZ = 1; TZ <= a.od && TZ * TX <= 96; TZ++) {
+    for (int TX = a.ow; TX > 0; TX = next_cut(a.ow, TX))
+        for (int TZ = a.od; TZ > 0; TZ = next_cut(a.od, TZ)) {
+            if (TX > 96 || TZ * TX > 96) continue;
             const int ns = (TZ * TX + 31) / 32, HX = (S * (TX - 1) + NT + 1) & ~1;
             const int tab = 128 * ns, gb = WTY * 32 * ns * grow, xb = TZ * RY * HX * xrow;
             if (tab + gb + xb > 60 * 1024) continue;
@@ -1322,9 +1450,9 @@ static bool wgrad_plan(const WgradArgs &a, WgradPlan &p)
             p.lds = tab + gb + xb > red ? tab + gb + xb : red;
         }
     if (best < 0.0) return false;
-    p.mTX = (unsigned)((0x100000000ull + p.TX - 1) / p.TX);
-    p.mHX = (unsigned)((0x100000000ull + p.HX - 1) / p.HX);
-    p.mNP = (unsigned)((0x100000000ull + 32 * p.ns - 1) / (32 * p.ns));
+    p.mTX = recip(p.TX);
+    p.mHX = recip(p.HX);
+    p.mNP = recip(32 * p.ns);
     p.tiles_x = (a.ow + p.TX - 1) / p.TX;
     p.tiles_y = (a.oh + WTY - 1) / WTY;
     p.tiles_z = (a.od + p.TZ - 1) / p.TZ;
