@@ -75,90 +75,118 @@ __device__ __forceinline__ bool tap_source(int kind, int z, int y, int x, int a,
     return true;
 }
 
-// ---------------------------------------------------------------- convolution (forward / dgrad)
-// One wave computes 64 consecutive output voxels (4 row fragments) x 16 NF
-// output channels.
-template <int NF>
-__global__ __launch_bounds__(256) void k_conv(ConvArgs a)
+// Four consecutive channels co .. co + 3 of output voxel v (bias and ReLU applied here).
+__device__ __forceinline__ void store4(const ConvArgs &a, long long v, int co, const f4 acc, const float bias[4], bool y8)
+{
+    float val[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        val[r] = acc[r] + bias[r];
+        if (a.relu) val[r] = fmaxf(val[r], 0.0f);
+    }
+    if (a.y) {
+        uint16_t *yp = a.y + v * a.cy + a.y_off + co;
+        if (y8 && co + 4 <= a.cout) {
+            *(uint2 *)yp = make_uint2(f2bf2(val[0], val[1]), f2bf2(val[2], val[3]));
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                if (co + r < a.cout) yp[r] = f2bf(val[r]);
+        }
+    }
+    if (a.y32) {
+        float *yp = a.y32 + v * a.cy32 + co;
+        if (co + 4 <= a.cout && a.cy32 % 4 == 0 && ((uintptr_t)a.y32 & 15) == 0) {
+            *(float4 *)yp = make_float4(val[0], val[1], val[2], val[3]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                if (co + r < a.cout) yp[r] = val[r];
+        }
+    }
+}
+
+// Whether a BF16 output slice takes 8-byte stores of four channels.
+__device__ __forceinline__ bool stores8(const ConvArgs &a)
+{
+    return a.cy % 4 == 0 && a.y_off % 4 == 0 && ((uintptr_t)a.y & 7) == 0;
+}
+
+__device__ __forceinline__ void load_bias4(const ConvArgs &a, int co, float bias[4])
+{
+#pragma unroll
+    for (int r = 0; r < 4; r++) bias[r] = a.bias && co + r < a.cout ? a.bias[co + r] : 0.0f;
+}
+
+// ---------------------------------------------------------------- convolution without halo reuse (2^3 stride 2, 1^3)
+// One wave computes 16 MF consecutive output voxels x 16 NF output channels
+// (block cg of ncg; the waves of a workgroup share the voxels' lines).  Each
+// input voxel meets one tap, so the fragments come straight from memory, and
+// what bounds the kernel is fetching their lines: a load takes 32 of a voxel's
+// bytes (the order of the sum is that of 16-channel chunks), so a wave covers
+// up to 64 output channels before another reads them again, and small grids
+// take fewer voxels per wave.  The weights are the MFMA's row operand (8-byte
+// stores).  Measured on 64 boxes of 40 x 24 x 40 (us, one wave per 64 voxels
+// and 2-byte stores before): stride 2 32 -> 64 104 (126), 64 -> 128 46 (86),
+// 1^3 head 52 (67).
+template <int MF, int NF, int KC>
+__global__ __launch_bounds__(256) void k_conv(ConvArgs a, int ncg)
 {
     const int lane = threadIdx.x & 63;
     const long long wave = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     const long long nvox = (long long)a.n * a.od * a.oh * a.ow;
-    const long long v0 = wave * 64;
+    const int cg = (int)(wave % ncg);
+    const long long v0 = wave / ncg * (16 * MF);
     if (v0 >= nvox) return;
     const int ks = ksize(a.kind);
     const int ntap = ks * ks * ks;
-    const int kc = a.cin / 16;
-    f4 acc[4][NF];
+    const int kc = KC ? KC : a.cin / 16, nft = (a.cout + 15) / 16, cn = cg * NF;
+    f4 acc[MF][NF];
 #pragma unroll
-    for (int f = 0; f < 4; f++)
+    for (int f = 0; f < MF; f++)
 #pragma unroll
         for (int n = 0; n < NF; n++) acc[f][n] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    // coordinates of this lane's A rows (one voxel per fragment)
-    int vz[4], vy[4], vx[4], vn[4];
-    bool vok[4];
+    // first input voxel of this lane's output voxels (one per fragment); past the end: the last voxel again
+    const int g = lane >> 4, i = lane & 15;
+    const uint16_t *src[MF];
 #pragma unroll
-    for (int f = 0; f < 4; f++) {
-        long long v = v0 + 16 * f + (lane & 15);
-        vok[f] = v < nvox;
-        if (!vok[f]) v = 0;
-        vx[f] = (int)(v % a.ow);
+    for (int f = 0; f < MF; f++) {
+        const long long v = min(v0 + 16 * f + i, nvox - 1);
+        const int x = (int)(v % a.ow);
         long long r = v / a.ow;
-        vy[f] = (int)(r % a.oh);
+        const int y = (int)(r % a.oh);
         r /= a.oh;
-        vz[f] = (int)(r % a.od);
-        vn[f] = (int)(r / a.od);
+        const int z = (int)(r % a.od), nn = (int)(r / a.od);
+        src[f] = a.x + (((((long long)nn * a.id + ks * z) * a.ih + ks * y) * a.iw + ks * x) * a.cx + a.x_off + 4 * g);
     }
-    const int kq = 4 * (lane >> 4);          // this lane's first K element within a fragment
+    const uint16_t *w = a.w + (size_t)cn * 256 + 4 * lane;
+#pragma unroll 2
     for (int t = 0; t < ntap; t++) {
-        const int ta = t / (ks * ks), tb = (t / ks) % ks, tc = t % ks;
-        long long src[4];
-        bool ok[4];
+        const long long off = (((long long)(t / (ks * ks)) * a.ih + (t / ks) % ks) * a.iw + t % ks) * a.cx;
 #pragma unroll
-        for (int f = 0; f < 4; f++) {
-            int sz = 0, sy = 0, sx = 0;
-            ok[f] = vok[f] && tap_source(a.kind, vz[f], vy[f], vx[f], ta, tb, tc, a.id, a.ih, a.iw, sz, sy, sx);
-            src[f] = ok[f] ? ((((long long)vn[f] * a.id + sz) * a.ih + sy) * a.iw + sx) * a.cx + a.x_off + kq : 0;
-        }
-        const uint16_t *wt = a.w + (size_t)t * kc * NF * 256;
         for (int c = 0; c < kc; c++) {
-            s4 A[4];
+            s4 A[MF];
 #pragma unroll
-            for (int f = 0; f < 4; f++) {
-                if (ok[f]) {
-                    const uint2 raw = *(const uint2 *)(a.x + src[f] + 16 * c);
-                    A[f] = s4{(short)(raw.x & 0xffff), (short)(raw.x >> 16), (short)(raw.y & 0xffff), (short)(raw.y >> 16)};
-                } else {
-                    A[f] = s4{0, 0, 0, 0};
-                }
-            }
+            for (int f = 0; f < MF; f++) A[f] = __builtin_bit_cast(s4, *(const uint2 *)(src[f] + off + 16 * c));
 #pragma unroll
             for (int n = 0; n < NF; n++) {
-                const uint2 raw = *(const uint2 *)(wt + ((size_t)c * NF + n) * 256 + 4 * lane);
-                const s4 Bv = s4{(short)(raw.x & 0xffff), (short)(raw.x >> 16), (short)(raw.y & 0xffff), (short)(raw.y >> 16)};
+                const s4 Bv = __builtin_bit_cast(s4, *(const uint2 *)(w + ((size_t)(t * kc + c) * nft + n) * 256));
 #pragma unroll
-                for (int f = 0; f < 4; f++) acc[f][n] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A[f], Bv, acc[f][n], 0, 0, 0);
+                for (int f = 0; f < MF; f++) acc[f][n] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Bv, A[f], acc[f][n], 0, 0, 0);
             }
         }
     }
-    // epilogue: D[i][j] -> voxel v0 + 16 f + 4 (lane/16) + r, channel 16 n + lane % 16
+    // D[row][col]: channel 16 (cn + n) + 4 g + r of voxel v0 + 16 f + i
+    const bool y8 = stores8(a);
 #pragma unroll
-    for (int f = 0; f < 4; f++)
+    for (int n = 0; n < NF; n++) {
+        const int co = 16 * (cn + n) + 4 * g;
+        float bias[4];
+        load_bias4(a, co, bias);
 #pragma unroll
-        for (int n = 0; n < NF; n++) {
-            const int co = 16 * n + (lane & 15);
-            if (co >= a.cout) continue;
-            const float bias = a.bias ? a.bias[co] : 0.0f;
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const long long v = v0 + 16 * f + 4 * (lane >> 4) + r;
-                if (v >= nvox) continue;
-                float val = acc[f][n][r] + bias;
-                if (a.relu) val = fmaxf(val, 0.0f);
-                if (a.y) a.y[v * a.cy + a.y_off + co] = f2bf(val);
-                if (a.y32) a.y32[v * a.cy32 + co] = val;
-            }
-        }
+        for (int f = 0; f < MF; f++)
+            if (v0 + 16 * f + i < nvox) store4(a, v0 + 16 * f + i, co, acc[f][n], bias, y8);
+    }
 }
 
 // ---------------------------------------------------------------- LDS-tiled convolution (3^3 and up)
@@ -246,87 +274,6 @@ __global__ __launch_bounds__(256) void k_conv_lds(ConvArgs a)
     const int oz = z0 + wv;
 #pragma unroll
     for (int f = 0; f < 4; f++) {
-        const int oy = y0 + f;
-        if (oz >= a.od || oy >= a.oh) continue;
-#pragma unroll
-        for (int n = 0; n < NF; n++) {
-            const int co = 16 * n + (lane & 15);
-            if (co >= a.cout) continue;
-            const float bias = a.bias ? a.bias[co] : 0.0f;
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int ox = x0 + 4 * (lane >> 4) + r;
-                if (ox >= a.ow) continue;
-                const long long v = (((long long)bn * a.od + oz) * a.oh + oy) * a.ow + ox;
-                float val = acc[f][n][r] + bias;
-                if (a.relu) val = fmaxf(val, 0.0f);
-                if (a.y) a.y[v * a.cy + a.y_off + co] = f2bf(val);
-                if (a.y32) a.y32[v * a.cy32 + co] = val;
-            }
-        }
-    }
-}
-
-// Epilogue of the LDS-tiled kernels: bias, ReLU and the outputs of a 4 x 4 x 16
-// tile (wave wv owns z-slice wv, fragment f row f, lane (i, g) voxels 4 g + r
-// of channel 16 n + i).  A BF16-only output slice (cout = 16 NF, 16-byte
-// aligned rows) goes through `ot` (LDS, >= 256 x (16 min(NF, 4) + 8) BF16,
-// free after the last barrier) and out as 16-byte rows.
-// Output channels per LDS pass of conv_store's fast path (its rows of 64 FR
-// voxels x (channels + 8) BF16 must fit the caller's LDS buffer).
-template <int NF, int FR>
-constexpr int store_pass_channels()
-{
-    return 16 * NF < (FR == 8 ? 32 : 64) ? 16 * NF : (FR == 8 ? 32 : 64);
-}
-
-// Epilogue of the tiled convolutions: wave wv holds FR rows (y) of 16 x
-// voxels of the z-slice z0 + wv, for all output channels.
-template <int NF, int FR = 4>
-__device__ __forceinline__ void conv_store(const ConvArgs &a, f4 (&acc)[FR][NF], int bn, int z0, int y0, int x0, int wv,
-                                           int lane, uint16_t *ot)
-{
-    constexpr int CO = 16 * NF;
-    const int g = lane >> 4, i = lane & 15;
-    const int oz = z0 + wv;
-    const bool fast = a.y && !a.y32 && a.cout == CO && (a.cy % 8) == 0 && (a.y_off % 8) == 0 &&
-                      ((uintptr_t)a.y & 15) == 0;
-    if (fast) {
-        // D[i][j] -> LDS row (wave, f, x = 4 (lane / 16) + r), channel 16 n + lane % 16; then 16-byte rows out
-        constexpr int CP = store_pass_channels<NF, FR>();
-        constexpr int NP = CO / CP;                           // channel passes
-        constexpr int PROW = CP + 8;
-#pragma unroll
-        for (int pass = 0; pass < NP; pass++) {
-#pragma unroll
-            for (int f = 0; f < FR; f++)
-#pragma unroll
-                for (int nn = 0; nn < NF / NP; nn++) {
-                    const int n = pass * (NF / NP) + nn;
-                    const float bias = a.bias ? a.bias[16 * n + i] : 0.0f;
-#pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        float val = acc[f][n][r] + bias;
-                        if (a.relu) val = fmaxf(val, 0.0f);
-                        ot[((wv * FR + f) * 16 + 4 * g + r) * PROW + 16 * nn + i] = f2bf(val);
-                    }
-                }
-            __syncthreads();
-            for (int e = threadIdx.x; e < 64 * FR * (CP / 8); e += 256) {
-                const int vl = e / (CP / 8), part = e % (CP / 8);
-                const int tz = vl / (16 * FR), ty = (vl >> 4) % FR, tx = vl & 15;
-                const int gz = z0 + tz, gy = y0 + ty, gx = x0 + tx;
-                if (gz < a.od && gy < a.oh && gx < a.ow) {
-                    const long long gv = (((long long)bn * a.od + gz) * a.oh + gy) * a.ow + gx;
-                    *(uint4 *)(a.y + gv * a.cy + a.y_off + pass * CP + 8 * part) = *(const uint4 *)(ot + vl * PROW + 8 * part);
-                }
-            }
-            if (pass + 1 < NP) __syncthreads();
-        }
-        return;
-    }
-#pragma unroll
-    for (int f = 0; f < FR; f++) {
         const int oy = y0 + f;
         if (oz >= a.od || oy >= a.oh) continue;
 #pragma unroll
@@ -495,41 +442,14 @@ __global__ __launch_bounds__((NF == 2 && FR == 8 ? 8 : 16) * 64) void k_conv_pos
     if (pos >= nreal || gz >= a.od || gx >= a.ow) return;
     float bias[NF][4];
 #pragma unroll
-    for (int n = 0; n < NF; n++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int co = 16 * (cn + n) + 4 * g + r;
-            bias[n][r] = a.bias && co < a.cout ? a.bias[co] : 0.0f;
-        }
-    const bool y8 = a.cy % 4 == 0 && a.y_off % 4 == 0 && ((uintptr_t)a.y & 7) == 0;   // 8-byte stores
+    for (int n = 0; n < NF; n++) load_bias4(a, 16 * (cn + n) + 4 * g, bias[n]);
+    const bool y8 = stores8(a);
 #pragma unroll
     for (int f = 0; f < FR; f++) {
         if (y0 + f >= a.oh) break;
         const long long v = (((long long)bn * a.od + gz) * a.oh + y0 + f) * a.ow + gx;
 #pragma unroll
-        for (int n = 0; n < NF; n++) {
-            const int co = 16 * (cn + n) + 4 * g;
-            float val[4];
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                val[r] = acc[f][n][r] + bias[n][r];
-                if (a.relu) val[r] = fmaxf(val[r], 0.0f);
-            }
-            if (a.y) {
-                uint16_t *yp = a.y + v * a.cy + a.y_off + co;
-                if (y8 && co + 4 <= a.cout) {
-                    *(uint2 *)yp = make_uint2(f2bf2(val[0], val[1]), f2bf2(val[2], val[3]));
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; r++)
-                        if (co + r < a.cout) yp[r] = f2bf(val[r]);
-                }
-            }
-            if (a.y32)
-#pragma unroll
-                for (int r = 0; r < 4; r++)
-                    if (co + r < a.cout) a.y32[v * a.cy32 + co + r] = val[r];
-        }
+        for (int n = 0; n < NF; n++) store4(a, v, 16 * (cn + n) + 4 * g, acc[f][n], bias[n], y8);
     }
 }
 
@@ -538,56 +458,75 @@ __global__ __launch_bounds__((NF == 2 && FR == 8 ? 8 : 16) * 64) void k_conv_pos
 // tap 4 c + g and its 8 elements are the 8 channels of that tap's input voxel
 // (one 16-byte LDS read); 7 steps cover the 27 taps (the 28th has zero
 // weights and reads tap 26's voxel).  The halo holds 8 channels per voxel.
+// Tiles as k_conv_pos (four waves of 16 positions, 4 rows, all channels); memory
+// bounds it (235 MB on 64 boxes of 40 x 24 x 40 in 88 us).
 constexpr int FIRST_STEPS = 7;
+constexpr int FIRST_ROWS = 4;
 
 template <int NF>
-__global__ __launch_bounds__(256, 2) void k_conv_first(ConvArgs a)
+__global__ __launch_bounds__(256) void k_conv_first(ConvArgs a, ConvPlan p)
 {
-    constexpr int NH = HLZ * HLY * HLX;
-    constexpr int OBUF = (256 * (16 * (NF < 4 ? NF : 4) + 8) * 2 + 15) / 16;   // epilogue rows, in uint4
-    __shared__ uint4 lds[NH > OBUF ? NH : OBUF];
+    typedef __attribute__((address_space(3))) void lds_void;
+    typedef const __attribute__((address_space(1))) void glob_void;
+    constexpr int FR = FIRST_ROWS, HY = FR + 2;
+    extern __shared__ uint4 halo[];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int tiles_x = (a.ow + TLX - 1) / TLX, tiles_y = (a.oh + TLY - 1) / TLY, tiles_z = (a.od + TLZ - 1) / TLZ;
-    int b = blockIdx.x;
-    const int bx = b % tiles_x;
-    b /= tiles_x;
-    const int by = b % tiles_y;
-    b /= tiles_y;
-    const int bz = b % tiles_z;
-    const int bn = b / tiles_z;
-    const int z0 = bz * TLZ, y0 = by * TLY, x0 = bx * TLX;
-    const uint16_t *xb = a.x + (long long)bn * a.id * a.ih * a.iw * a.cx + a.x_off;
-    for (int v = threadIdx.x; v < NH; v += 256) {
-        const int lx = v % HLX, ly = (v / HLX) % HLY, lz = v / (HLX * HLY);
+    const int per = (p.ntiles + 7) >> 3, tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || tile >= p.ntiles) return;
+    int b = tile;
+    const int x0 = (b % p.tiles_x) * p.TX;
+    b /= p.tiles_x;
+    const int y0 = (b % p.tiles_y) * FR;
+    b /= p.tiles_y;
+    const int z0 = (b % p.tiles_z) * p.TZ, bn = b / p.tiles_z;
+    const uint16_t *xb = a.x + (size_t)bn * a.id * a.ih * a.iw * a.cx + a.x_off;
+    const int nh = p.HZ * HY * p.HX;
+    for (int s0 = 64 * wv; s0 < nh; s0 += 256) {
+        const int v = s0 + lane;
+        if (v >= nh) break;
+        const int q = div_by(v, p.mHX, p.HX), lx = v - q * p.HX, lz = q / HY, ly = q - lz * HY;
         const int gz = z0 - 1 + lz, gy = y0 - 1 + ly, gx = x0 - 1 + lx;
-        uint4 val = make_uint4(0u, 0u, 0u, 0u);
-        if (gz >= 0 && gy >= 0 && gx >= 0 && gz < a.id && gy < a.ih && gx < a.iw)
-            val = *(const uint4 *)(xb + (((long long)gz * a.ih + gy) * a.iw + gx) * a.cx);
-        lds[v] = val;
+        const bool in = gz >= 0 && gy >= 0 && gx >= 0 && gz < a.id && gy < a.ih && gx < a.iw;
+        const uint16_t *src = in ? xb + (size_t)(unsigned)((gz * a.ih + gy) * a.iw + gx) * a.cx : g_zero_piece;
+        __builtin_amdgcn_global_load_lds((glob_void *)src, (lds_void *)(halo + s0), 16, 0, 0);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies are not tracked by the compiler
     __syncthreads();
-    f4 acc[4][NF];
+    f4 acc[FR][NF];
 #pragma unroll
-    for (int f = 0; f < 4; f++)
+    for (int f = 0; f < FR; f++)
 #pragma unroll
         for (int n = 0; n < NF; n++) acc[f][n] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     const int g = lane >> 4, i = lane & 15;
+    const int pos = 16 * wv + i, nreal = p.TZ * p.TX;
+    const int pz = pos < nreal ? div_by(pos, p.mTX, p.TX) : 0, px = pos < nreal ? pos - pz * p.TX : 0;
+    const int base = pz * HY * p.HX + px;
 #pragma unroll
     for (int c = 0; c < FIRST_STEPS; c++) {
         const int t = min(4 * c + g, 26);
         const int ta = t / 9, tb = (t / 3) % 3, tc = t % 3;
-        b8 A[4];
+        b8 A[FR];
 #pragma unroll
-        for (int f = 0; f < 4; f++) A[f] = __builtin_bit_cast(b8, lds[((wv + ta) * HLY + f + tb) * HLX + i + tc]);
+        for (int f = 0; f < FR; f++) A[f] = __builtin_bit_cast(b8, halo[base + (ta * HY + f + tb) * p.HX + tc]);
 #pragma unroll
         for (int n = 0; n < NF; n++) {
             const b8 Bv = __builtin_bit_cast(b8, *(const uint4 *)(a.w + ((size_t)(c * NF + n) * 64 + lane) * 8));
 #pragma unroll
-            for (int f = 0; f < 4; f++) acc[f][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[f], Bv, acc[f][n], 0, 0, 0);
+            for (int f = 0; f < FR; f++) acc[f][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Bv, A[f], acc[f][n], 0, 0, 0);
         }
     }
-    __syncthreads();   // the epilogue reuses the halo's LDS
-    conv_store<NF>(a, acc, bn, z0, y0, x0, wv, lane, (uint16_t *)lds);
+    const int gz = z0 + pz, gx = x0 + px;
+    if (pos >= nreal || gz >= a.od || gx >= a.ow) return;
+    const bool y8 = stores8(a);
+#pragma unroll
+    for (int n = 0; n < NF; n++) {
+        float bias[4];
+        load_bias4(a, 16 * n + 4 * g, bias);
+#pragma unroll
+        for (int f = 0; f < FR; f++)
+            if (y0 + f < a.oh)
+                store4(a, (((long long)bn * a.od + gz) * a.oh + y0 + f) * a.ow + gx, 16 * n + 4 * g, acc[f][n], bias, y8);
+    }
 }
 
 // Pack FP32 master weights W[tap][ci][co] (ci < cin, co < cout) into the
@@ -892,7 +831,9 @@ __global__ __launch_bounds__(64 * NW) void k_reduce_partials(const float *partia
 // sums a chunk of voxels for every channel (consecutive threads read
 // consecutive channels of a voxel), reduces in LDS and adds its partial sums
 // with one float atomic per channel; gb is cleared first unless accumulating.
-constexpr int BIAS_CHUNK = 8192;
+// The voxels are cut into about 512 chunks, two workgroups per CU (at 8,192
+// voxels a chunk the largest layer of a training batch had 38 workgroups and
+// took 80 us; the 512 atomics per channel do not show).
 
 __global__ void k_fill_f(float *p, int n, float v)
 {
@@ -901,12 +842,12 @@ __global__ void k_fill_f(float *p, int n, float v)
 }
 
 __global__ __launch_bounds__(256) void k_bias_grad(const uint16_t *g, long long nvox, int cg, int g_off, int cout,
-                                                   float *gb)
+                                                   float *gb, int chunk)
 {
     __shared__ float red[256];
     const int vl = 256 / cout;                       // voxel lanes (cout <= 128)
     const int co = threadIdx.x % cout, lv = threadIdx.x / cout;
-    const long long v0 = (long long)blockIdx.x * BIAS_CHUNK, v1 = min(nvox, v0 + BIAS_CHUNK);
+    const long long v0 = (long long)blockIdx.x * chunk, v1 = min(nvox, v0 + chunk);
     float sum = 0.0f;
     if (lv < vl)
         for (long long v = v0 + lv; v < v1; v += vl) sum += bf2f(g[v * cg + g_off + co]);
@@ -922,13 +863,13 @@ __global__ __launch_bounds__(256) void k_bias_grad(const uint16_t *g, long long 
 // The same sum with 4 channels per thread (8-byte loads) and four voxels in
 // flight per thread; needs cout, cg and g_off multiples of 4.
 __global__ __launch_bounds__(256) void k_bias_grad4(const uint16_t *g, long long nvox, int cg, int g_off, int cout,
-                                                    float *gb)
+                                                    float *gb, int chunk)
 {
     __shared__ float red[256 * 4];
     const int cq = cout / 4;                         // threads per voxel
     const int vl = 256 / cq;                         // voxel lanes
     const int q = threadIdx.x % cq, lv = threadIdx.x / cq;
-    const long long v0 = (long long)blockIdx.x * BIAS_CHUNK, v1 = min(nvox, v0 + BIAS_CHUNK);
+    const long long v0 = (long long)blockIdx.x * chunk, v1 = min(nvox, v0 + chunk);
     float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (lv < vl) {
         const uint16_t *gp = g + g_off + 4 * q;
@@ -975,6 +916,28 @@ __global__ void k_relu_bwd(uint16_t *g, int cg, int g_off, const uint16_t *y, in
     }
 }
 
+// The same with 8 channels per thread (16-byte loads and stores; c = 8 << cs): one
+// channel per thread spent its time on the index divisions.
+__global__ __launch_bounds__(256) void k_relu_bwd8(uint16_t *g, int cg, int g_off, const uint16_t *y, int cy, int y_off,
+                                                   long long n, int cs)
+{
+    for (long long e = blockIdx.x * 256LL + threadIdx.x; e < n; e += (long long)gridDim.x * 256) {
+        const long long v = e >> cs;
+        const int c = 8 * (int)(e & ((1 << cs) - 1));
+        uint4 *gp = (uint4 *)(g + v * cg + g_off + c);
+        const uint4 yv = *(const uint4 *)(y + v * cy + y_off + c);
+        uint4 gv = *gp;
+        auto keep = [](uint32_t gw, uint32_t yw) {
+            return (bf2f((uint16_t)yw) > 0.0f ? gw & 0xffffu : 0u) | (bf2f((uint16_t)(yw >> 16)) > 0.0f ? gw & 0xffff0000u : 0u);
+        };
+        gv.x = keep(gv.x, yv.x);
+        gv.y = keep(gv.y, yv.y);
+        gv.z = keep(gv.z, yv.z);
+        gv.w = keep(gv.w, yv.w);
+        *gp = gv;
+    }
+}
+
 // coarse[U] = sum of the 8 fine children (nearest-upsampling backward)
 __global__ void k_up_bwd(const uint16_t *fine, int cf, int f_off, uint16_t *coarse, int cc, int c_off, int n, int d, int h,
                          int w, int c)
@@ -997,6 +960,38 @@ __global__ void k_up_bwd(const uint16_t *fine, int cf, int f_off, uint16_t *coar
                     s += bf2f(fine[fv * cf + f_off + ch]);
                 }
         coarse[v * cc + c_off + ch] = f2bf(s);
+    }
+}
+
+// The same with 8 channels per thread (c = 8 << cs).
+__global__ __launch_bounds__(256) void k_up_bwd8(const uint16_t *fine, int cf, int f_off, uint16_t *coarse, int cc, int c_off,
+                                                 int n, int d, int h, int w, int cs)
+{
+    const long long total = ((long long)n * d * h * w) << cs;
+    for (long long e = blockIdx.x * 256LL + threadIdx.x; e < total; e += (long long)gridDim.x * 256) {
+        const int ch = 8 * (int)(e & ((1 << cs) - 1));
+        const long long v = e >> cs;
+        const int x = (int)(v % w);
+        long long q = v / w;
+        const int y = (int)(q % h);
+        q /= h;
+        const int z = (int)(q % d), nn = (int)(q / d);
+        const uint16_t *f = fine + ((((long long)nn * 2 * d + 2 * z) * 2 * h + 2 * y) * 2 * w + 2 * x) * cf + f_off + ch;
+        uint4 r[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+            r[k] = *(const uint4 *)(f + (((long long)(k >> 2) * 2 * h + ((k >> 1) & 1)) * 2 * w + (k & 1)) * cf);
+        float s[8] = {};
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const uint32_t u[4] = {r[k].x, r[k].y, r[k].z, r[k].w};
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                s[2 * j] += __uint_as_float(u[j] << 16);
+                s[2 * j + 1] += __uint_as_float(u[j] & 0xffff0000u);
+            }
+        }
+        *(uint4 *)(coarse + v * cc + c_off + ch) = make_uint4(f2bf2(s[0], s[1]), f2bf2(s[2], s[3]), f2bf2(s[4], s[5]), f2bf2(s[6], s[7]));
     }
 }
 
@@ -1027,70 +1022,75 @@ __global__ void k_down_dgrad(const uint16_t *g, int cg, int g_off, const float *
 }
 
 // The same adjoint on MFMA: for each of the 8 taps t it is a GEMM
-//   D[coarse voxel V][ci] = sum_co dY[V][co] W[t][ci][co]
-// whose result lands on the fine voxel 2 V + t.  A wave owns 64 coarse voxels
-// (4 row fragments) and all cin = 16 NF input channels; the FP32 weights are
-// rounded to BF16 as they are read into the B fragments.
-template <int NF>
+//   D[ci][coarse voxel V] = sum_co W[t][ci][co] dY[V][co]
+// whose result lands on the fine voxel 2 V + t.  A wave owns one tap
+// (blockIdx.y), 16 MF coarse voxels and 16 NF input channels; the FP32 weights
+// are the row operand, rounded to BF16 as they are read, so that a lane ends
+// with four channels of one voxel (8-byte stores).  One wave over all eight
+// taps with 2-byte stores kept too few bytes in flight: 245 and 137 us on the
+// two stride-2 layers of a training batch.
+template <int MF, int NF>
 __global__ __launch_bounds__(256) void k_down_dgrad_mfma(const uint16_t *g, int cg, int g_off, const float *w, int cin,
                                                          int cout, uint16_t *gx, int cx, int x_off, int n, int d, int h,
-                                                         int wd, int accumulate)
+                                                         int wd, int accumulate, int ncb)
 {
     const int lane = threadIdx.x & 63, i = lane & 15, gq = lane >> 4;
     const int D2 = d / 2, H2 = h / 2, W2 = wd / 2;
-    const int nvc = n * D2 * H2 * W2;
-    const int V0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
+    const int nvc = n * D2 * H2 * W2, t = blockIdx.y;
+    const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int cb = wave % ncb * 16 * NF, V0 = wave / ncb * (16 * MF);
     if (V0 >= nvc) return;
-    // fine index of tap 0 for the coarse voxels of this lane's D rows (f, r)
-    int fb[4][4];
-#pragma unroll
-    for (int f = 0; f < 4; f++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int V = V0 + 16 * f + 4 * gq + r;
-            if (V >= nvc) { fb[f][r] = -1; continue; }
-            const int x = V % W2, y = (V / W2) % H2, z = (V / (W2 * H2)) % D2, nn = V / (W2 * H2 * D2);
-            fb[f][r] = ((nn * d + 2 * z) * h + 2 * y) * wd + 2 * x;
-        }
     const int kc = cout / 16;
-    for (int t = 0; t < 8; t++) {
-        const int ta = t >> 2, tb = (t >> 1) & 1, tc = t & 1;
-        f4 acc[4][NF];
+    const uint16_t *gp[MF];
 #pragma unroll
-        for (int f = 0; f < 4; f++)
+    for (int f = 0; f < MF; f++) gp[f] = g + (long long)min(V0 + 16 * f + i, nvc - 1) * cg + g_off + 4 * gq;
+    const float *wp = w + ((long long)t * cin + cb + i) * cout + 4 * gq;
+    f4 acc[MF][NF];
 #pragma unroll
-            for (int nf = 0; nf < NF; nf++) acc[f][nf] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-        for (int c = 0; c < kc; c++) {
-            s4 A[4];
+    for (int f = 0; f < MF; f++)
 #pragma unroll
-            for (int f = 0; f < 4; f++) {
-                const int V = V0 + 16 * f + i;
-                uint2 raw = make_uint2(0u, 0u);
-                if (V < nvc) raw = *(const uint2 *)(g + (long long)V * cg + g_off + 16 * c + 4 * gq);
-                A[f] = s4{(short)(raw.x & 0xffff), (short)(raw.x >> 16), (short)(raw.y & 0xffff), (short)(raw.y >> 16)};
-            }
+        for (int nf = 0; nf < NF; nf++) acc[f][nf] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+    for (int c = 0; c < kc; c++) {
+        s4 A[MF];
 #pragma unroll
-            for (int nf = 0; nf < NF; nf++) {
-                const float4 wv = *(const float4 *)(w + ((long long)t * cin + 16 * nf + i) * cout + 16 * c + 4 * gq);
-                const s4 Bv = s4{(short)f2bf(wv.x), (short)f2bf(wv.y), (short)f2bf(wv.z), (short)f2bf(wv.w)};
+        for (int f = 0; f < MF; f++) A[f] = __builtin_bit_cast(s4, *(const uint2 *)(gp[f] + 16 * c));
 #pragma unroll
-                for (int f = 0; f < 4; f++) acc[f][nf] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A[f], Bv, acc[f][nf], 0, 0, 0);
+        for (int nf = 0; nf < NF; nf++) {
+            const float4 wv = *(const float4 *)(wp + (long long)nf * 16 * cout + 16 * c);
+            const s4 Bv = __builtin_bit_cast(s4, make_uint2(f2bf2(wv.x, wv.y), f2bf2(wv.z, wv.w)));
+#pragma unroll
+            for (int f = 0; f < MF; f++) acc[f][nf] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Bv, A[f], acc[f][nf], 0, 0, 0);
+        }
+    }
+    const bool x8 = cx % 4 == 0 && x_off % 4 == 0 && ((uintptr_t)gx & 7) == 0;
+#pragma unroll
+    for (int f = 0; f < MF; f++) {
+        const int V = V0 + 16 * f + i;
+        if (V >= nvc) continue;
+        const int x = V % W2, y = (V / W2) % H2, z = (V / (W2 * H2)) % D2, nn = V / (W2 * H2 * D2);
+        const long long fine = ((long long)(nn * d + 2 * z + (t >> 2)) * h + 2 * y + ((t >> 1) & 1)) * wd + 2 * x + (t & 1);
+        uint16_t *op = gx + fine * cx + x_off + cb + 4 * gq;
+#pragma unroll
+        for (int nf = 0; nf < NF; nf++) {
+            float val[4];
+            uint16_t *o = op + 16 * nf;
+            if (x8) {
+                const uint2 old = accumulate ? *(const uint2 *)o : make_uint2(0u, 0u);
+#pragma unroll
+                for (int r = 0; r < 4; r++) val[r] = acc[f][nf][r];
+                if (accumulate) {
+                    val[0] += __uint_as_float(old.x << 16);
+                    val[1] += __uint_as_float(old.x & 0xffff0000u);
+                    val[2] += __uint_as_float(old.y << 16);
+                    val[3] += __uint_as_float(old.y & 0xffff0000u);
+                }
+                *(uint2 *)o = make_uint2(f2bf2(val[0], val[1]), f2bf2(val[2], val[3]));
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; r++) o[r] = f2bf(accumulate ? acc[f][nf][r] + bf2f(o[r]) : acc[f][nf][r]);
             }
         }
-        const int toff = (ta * h + tb) * wd + tc;
-#pragma unroll
-        for (int f = 0; f < 4; f++)
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                if (fb[f][r] < 0) continue;
-                uint16_t *gp = gx + (long long)(fb[f][r] + toff) * cx + x_off + i;
-#pragma unroll
-                for (int nf = 0; nf < NF; nf++) {
-                    float val = acc[f][nf][r];
-                    if (accumulate) val += bf2f(gp[16 * nf]);
-                    gp[16 * nf] = f2bf(val);
-                }
-            }
     }
 }
 
@@ -1101,6 +1101,28 @@ __global__ void k_to_bf16(const float *x, int cs, long long nvox, int c, uint16_
         long long v = e / c_pad;
         int ch = (int)(e % c_pad);
         y[v * cy + y_off + ch] = ch < c ? f2bf(x[v * cs + ch]) : (uint16_t)0;
+    }
+}
+
+// The same with 8 channels per thread (c_pad = 8 << ps; x4: rows of whole float4).
+__global__ __launch_bounds__(256) void k_to_bf16_8(const float *x, int cs, long long n, int c, uint16_t *y, int cy, int y_off,
+                                                   int ps, int x4)
+{
+    for (long long e = blockIdx.x * 256LL + threadIdx.x; e < n; e += (long long)gridDim.x * 256) {
+        const long long v = e >> ps;
+        const int c0 = 8 * (int)(e & ((1 << ps) - 1));
+        const float *xp = x + v * cs + c0;
+        float f[8] = {};
+        if (x4 && c0 + 8 <= c) {
+            const float4 a = *(const float4 *)xp, b = *(const float4 *)(xp + 4);
+            f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w;
+            f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; k++)
+                if (c0 + k < c) f[k] = xp[k];
+        }
+        *(uint4 *)(y + v * cy + y_off + c0) = make_uint4(f2bf2(f[0], f[1]), f2bf2(f[2], f[3]), f2bf2(f[4], f[5]), f2bf2(f[6], f[7]));
     }
 }
 
@@ -1354,7 +1376,6 @@ template <int KIND>
 static hipError_t conv_lds(const ConvArgs &a, hipStream_t st)
 {
     const int nf = (a.cout + 15) / 16;
-    if (nf != 1 && nf != 2 && nf != 4 && nf != 8) return hipErrorInvalidValue;
     if (a.cin % 32 == 0)   // the weights were packed as 16x16x32 fragments (same condition in pack)
         return nf == 1 ? conv_pos<1, KIND>(a, st) : conv_pos<2, KIND>(a, st);
     const long long tiles = (long long)a.n * ((a.od + TLZ - 1) / TLZ) * ((a.oh + TLY - 1) / TLY) * ((a.ow + TLX - 1) / TLX);
@@ -1369,33 +1390,79 @@ static hipError_t conv_lds(const ConvArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
+// Tile of the first layer: the least padded positions, then the smallest halo.
+static bool first_plan(const ConvArgs &a, ConvPlan &p)
+{
+    double best = -1.0;
+    for (int TX = a.ow; TX > 0; TX = next_cut(a.ow, TX))
+        for (int TZ = a.od; TZ > 0; TZ = next_cut(a.od, TZ)) {
+            if (TX > 64 || TZ * TX > 64) continue;
+            const double tiles = (double)((a.ow + TX - 1) / TX) * ((a.od + TZ - 1) / TZ);
+            const double cost = tiles * (64 * 32 + 2.0 * (TZ + 2) * (TX + 2));
+            if (best >= 0.0 && cost >= best) continue;
+            best = cost;
+            p.TX = TX; p.TZ = TZ;
+        }
+    p.HX = p.TX + 2; p.HZ = p.TZ + 2; p.HY = FIRST_ROWS + 2;
+    p.tiles_x = (a.ow + p.TX - 1) / p.TX;
+    p.tiles_y = (a.oh + FIRST_ROWS - 1) / FIRST_ROWS;
+    p.tiles_z = (a.od + p.TZ - 1) / p.TZ;
+    const long long nt = (long long)a.n * p.tiles_x * p.tiles_y * p.tiles_z;
+    if (nt > 0x7ffffff0) return false;
+    p.ntiles = (int)nt;
+    p.mTX = recip(p.TX);
+    p.mHX = recip(p.HX);
+    p.lds = 16 * p.HZ * p.HY * p.HX;
+    return true;
+}
+
+template <int NF, int KC>
+static hipError_t conv_direct_kc(const ConvArgs &a, hipStream_t st)
+{
+    const long long nvox = (long long)a.n * a.od * a.oh * a.ow;
+    const int ncg = (a.cout + 16 * NF - 1) / (16 * NF);
+    // voxels per wave: 64, or fewer while the launch has less than 32 waves per CU
+    int mf = 4;
+    while (mf > 1 && (nvox + 16 * mf - 1) / (16 * mf) * ncg < 8192) mf /= 2;
+    const long long wgs = ((nvox + 16 * mf - 1) / (16 * mf) * ncg + 3) / 4;
+    if (wgs > 0x7fffffff) return hipErrorInvalidValue;
+    const unsigned g = (unsigned)wgs;
+    if (mf == 4) k_conv<4, NF, KC><<<g, 256, 0, st>>>(a, ncg);
+    else if (mf == 2) k_conv<2, NF, KC><<<g, 256, 0, st>>>(a, ncg);
+    else k_conv<1, NF, KC><<<g, 256, 0, st>>>(a, ncg);
+    return hipGetLastError();
+}
+
+template <int NF>
+static hipError_t conv_direct(const ConvArgs &a, hipStream_t st)
+{
+    if (a.cin == 32) return conv_direct_kc<NF, 2>(a, st);
+    if (a.cin == 64) return conv_direct_kc<NF, 4>(a, st);
+    return conv_direct_kc<NF, 0>(a, st);
+}
+
 hipError_t conv(const ConvArgs &a, hipStream_t st)
 {
+    const int nf = (a.cout + 15) / 16;
+    if (nf != 1 && nf != 2 && nf != 4 && nf != 8) return hipErrorInvalidValue;
     if (a.kind == KIND_C3 && a.cin == 8) {
-        if (a.cx % 8 || a.x_off % 8 || ((uintptr_t)a.x & 15)) return hipErrorInvalidValue;
-        const long long tiles = (long long)a.n * ((a.od + TLZ - 1) / TLZ) * ((a.oh + TLY - 1) / TLY) * ((a.ow + TLX - 1) / TLX);
-        if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-        switch ((a.cout + 15) / 16) {
-        case 1: k_conv_first<1><<<(unsigned)tiles, 256, 0, st>>>(a); break;
-        case 2: k_conv_first<2><<<(unsigned)tiles, 256, 0, st>>>(a); break;
-        case 4: k_conv_first<4><<<(unsigned)tiles, 256, 0, st>>>(a); break;
-        case 8: k_conv_first<8><<<(unsigned)tiles, 256, 0, st>>>(a); break;
-        default: return hipErrorInvalidValue;
+        ConvPlan p{};
+        if (a.cx % 8 || a.x_off % 8 || ((uintptr_t)a.x & 15) || !first_plan(a, p)) return hipErrorInvalidValue;
+        const unsigned g = (unsigned)((p.ntiles + 7) / 8 * 8);
+        switch (nf) {
+        case 1: k_conv_first<1><<<g, 256, p.lds, st>>>(a, p); break;
+        case 2: k_conv_first<2><<<g, 256, p.lds, st>>>(a, p); break;
+        case 4: k_conv_first<4><<<g, 256, p.lds, st>>>(a, p); break;
+        case 8: k_conv_first<8><<<g, 256, p.lds, st>>>(a, p); break;
         }
         return hipGetLastError();
     }
     if (a.kind == KIND_C3) return conv_lds<KIND_C3>(a, st);
     if (a.kind == KIND_UP) return conv_lds<KIND_UP>(a, st);
+    if (nf == 1) return conv_direct<1>(a, st);
+    // 64 channels per wave read each input line once for them; on small grids 32, for more waves
     const long long nvox = (long long)a.n * a.od * a.oh * a.ow;
-    const unsigned g = (unsigned)((nvox + 255) / 256);
-    switch ((a.cout + 15) / 16) {
-    case 1: k_conv<1><<<g, 256, 0, st>>>(a); break;
-    case 2: k_conv<2><<<g, 256, 0, st>>>(a); break;
-    case 4: k_conv<4><<<g, 256, 0, st>>>(a); break;
-    case 8: k_conv<8><<<g, 256, 0, st>>>(a); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return nf >= 4 && (nvox + 15) / 16 * (nf / 4) >= 2048 ? conv_direct<4>(a, st) : conv_direct<2>(a, st);
 }
 
 hipError_t pack(const float *w, int ntap, int cin, int cout, int cin_p, int cout_p, int transpose, uint16_t *out,
@@ -1510,17 +1577,31 @@ hipError_t bias_grad(const uint16_t *g, long long nvox, int cg, int g_off, int c
 {
     if (cout > 128) return hipErrorInvalidValue;
     if (!accumulate) k_fill_f<<<(cout + 63) / 64, 64, 0, st>>>(gb, cout, 0.0f);
-    const long long nb = (nvox + BIAS_CHUNK - 1) / BIAS_CHUNK;
+    const long long chunk = std::min(std::max(256LL, (nvox + 511) / 512), 1LL << 20);
+    const long long nb = (nvox + chunk - 1) / chunk;
     if (cout % 4 == 0 && cg % 4 == 0 && g_off % 4 == 0 && ((uintptr_t)g & 7) == 0)
-        k_bias_grad4<<<(unsigned)nb, 256, 0, st>>>(g, nvox, cg, g_off, cout, gb);
+        k_bias_grad4<<<(unsigned)nb, 256, 0, st>>>(g, nvox, cg, g_off, cout, gb, (int)chunk);
     else
-        k_bias_grad<<<(unsigned)nb, 256, 0, st>>>(g, nvox, cg, g_off, cout, gb);
+        k_bias_grad<<<(unsigned)nb, 256, 0, st>>>(g, nvox, cg, g_off, cout, gb, (int)chunk);
     return hipGetLastError();
+}
+
+// log2(c / 8) when c is 8 times a power of two, else -1.
+static int vec8(int c)
+{
+    for (int s = 0; s < 8; s++)
+        if (c == 8 << s) return s;
+    return -1;
 }
 
 hipError_t relu_bwd(uint16_t *g, int cg, int g_off, const uint16_t *y, int cy, int y_off, long long nvox, int c,
                     hipStream_t st)
 {
+    const int cs = vec8(c);
+    if (cs >= 0 && cg % 8 == 0 && g_off % 8 == 0 && cy % 8 == 0 && y_off % 8 == 0 && !(((uintptr_t)g | (uintptr_t)y) & 15)) {
+        k_relu_bwd8<<<grid_for(nvox << cs), 256, 0, st>>>(g, cg, g_off, y, cy, y_off, nvox << cs, cs);
+        return hipGetLastError();
+    }
     k_relu_bwd<<<grid_for(nvox * c), 256, 0, st>>>(g, cg, g_off, y, cy, y_off, nvox, c);
     return hipGetLastError();
 }
@@ -1528,6 +1609,11 @@ hipError_t relu_bwd(uint16_t *g, int cg, int g_off, const uint16_t *y, int cy, i
 hipError_t up_bwd(const uint16_t *fine, int cf, int f_off, uint16_t *coarse, int cc, int c_off, int n, int d, int h, int w,
                   int c, hipStream_t st)
 {
+    const int cs = vec8(c);
+    if (cs >= 0 && cf % 8 == 0 && f_off % 8 == 0 && cc % 8 == 0 && c_off % 8 == 0 && !(((uintptr_t)fine | (uintptr_t)coarse) & 15)) {
+        k_up_bwd8<<<grid_for(((long long)n * d * h * w) << cs), 256, 0, st>>>(fine, cf, f_off, coarse, cc, c_off, n, d, h, w, cs);
+        return hipGetLastError();
+    }
     k_up_bwd<<<grid_for((long long)n * d * h * w * c), 256, 0, st>>>(fine, cf, f_off, coarse, cc, c_off, n, d, h, w, c);
     return hipGetLastError();
 }
@@ -1539,16 +1625,13 @@ hipError_t down_dgrad(const uint16_t *g, int cg, int g_off, const float *w, int 
     if (cin % 16 == 0 && cout % 16 == 0 && cin <= 128 && cg % 4 == 0 && g_off % 4 == 0 && nfine < 0x7fffffffLL &&
         ((uintptr_t)g & 7) == 0 && ((uintptr_t)w & 15) == 0) {
         const long long nvc = nfine / 8;
-        const unsigned blocks = (unsigned)((nvc + 255) / 256);
-        switch (cin / 16) {
-        case 1: k_down_dgrad_mfma<1><<<blocks, 256, 0, st>>>(g, cg, g_off, w, cin, cout, gx, cx, x_off, n, d, h, wd, accumulate); break;
-        case 2: k_down_dgrad_mfma<2><<<blocks, 256, 0, st>>>(g, cg, g_off, w, cin, cout, gx, cx, x_off, n, d, h, wd, accumulate); break;
-        case 4: k_down_dgrad_mfma<4><<<blocks, 256, 0, st>>>(g, cg, g_off, w, cin, cout, gx, cx, x_off, n, d, h, wd, accumulate); break;
-        case 8: k_down_dgrad_mfma<8><<<blocks, 256, 0, st>>>(g, cg, g_off, w, cin, cout, gx, cx, x_off, n, d, h, wd, accumulate); break;
-        default:
-            k_down_dgrad<<<grid_for(nfine * cin), 256, 0, st>>>(g, cg, g_off, w, cin, cout, gx, cx, x_off, n, d, h, wd,
-                                                                accumulate);
-        }
+        const int nf = cin / 16 % 2 ? 1 : 2, ncb = cin / (16 * nf);
+        const int mf = (nvc + 63) / 64 * ncb * 8 < 4096 ? 1 : 4;      // voxels per wave: 64, fewer on small grids
+        const dim3 blocks((unsigned)(((nvc + 16 * mf - 1) / (16 * mf) * ncb + 3) / 4), 8);
+        if (nf == 2 && mf == 4) k_down_dgrad_mfma<4, 2><<<blocks, 256, 0, st>>>(g, cg, g_off, w, cin, cout, gx, cx, x_off, n, d, h, wd, accumulate, ncb);
+        else if (nf == 2) k_down_dgrad_mfma<1, 2><<<blocks, 256, 0, st>>>(g, cg, g_off, w, cin, cout, gx, cx, x_off, n, d, h, wd, accumulate, ncb);
+        else if (mf == 4) k_down_dgrad_mfma<4, 1><<<blocks, 256, 0, st>>>(g, cg, g_off, w, cin, cout, gx, cx, x_off, n, d, h, wd, accumulate, ncb);
+        else k_down_dgrad_mfma<1, 1><<<blocks, 256, 0, st>>>(g, cg, g_off, w, cin, cout, gx, cx, x_off, n, d, h, wd, accumulate, ncb);
         return hipGetLastError();
     }
     k_down_dgrad<<<grid_for(nfine * cin), 256, 0, st>>>(g, cg, g_off, w, cin, cout, gx, cx, x_off, n, d, h, wd, accumulate);
@@ -1557,6 +1640,12 @@ hipError_t down_dgrad(const uint16_t *g, int cg, int g_off, const float *w, int 
 
 hipError_t to_bf16(const float *x, int cs, long long nvox, int c, uint16_t *y, int cy, int y_off, int c_pad, hipStream_t st)
 {
+    const int ps = vec8(c_pad);
+    if (ps >= 0 && cy % 8 == 0 && y_off % 8 == 0 && !((uintptr_t)y & 15)) {
+        const int x4 = cs % 4 == 0 && !((uintptr_t)x & 15);
+        k_to_bf16_8<<<grid_for(nvox << ps), 256, 0, st>>>(x, cs, nvox << ps, c, y, cy, y_off, ps, x4);
+        return hipGetLastError();
+    }
     k_to_bf16<<<grid_for(nvox * c_pad), 256, 0, st>>>(x, cs, nvox, c, y, cy, y_off, c_pad);
     return hipGetLastError();
 }
