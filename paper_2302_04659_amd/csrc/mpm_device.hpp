@@ -113,9 +113,9 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 
 __device__ __forceinline__ long long node_index(const SceneDev &S, int B, int i, int j, int k)
 {
-    int nb = S.nb;
-    int lb = ((i / B) * nb + (j / B)) * nb + (k / B);
-    int l = ((i % B) * B + (j % B)) * B + (k % B);
+    const unsigned nb = S.nb, ui = i, uj = j, uk = k, ub = B;   // unsigned: shifts and masks without sign fixes
+    const unsigned lb = ((ui / ub) * nb + (uj / ub)) * nb + (uk / ub);
+    const unsigned l = ((ui % ub) * ub + (uj % ub)) * ub + (uk % ub);
     return S.grid_off + (long long)lb * (B * B * B) + l;
 }
 
@@ -190,6 +190,49 @@ __device__ __forceinline__ void particle_base(const SceneK &K, float x, int &b, 
     clamped |= (c != bi) || !(fb == fb);
     b = c;
     f = xi - (float)c;
+}
+
+// The common case of particle_base inside one work item: a particle whose base
+// cell lies in the item's tile range and needs no clamping.  The base cell is
+// kept as floats (exact below 2^24): one comparison per bound rejects a NaN,
+// and the linear index takes two FMAs and one conversion.  Anything else goes
+// through particle_base.
+struct TileBox {
+    float lo[3], hi[3];
+};
+
+// org: first node of the tile, bmax: its largest base-cell coordinate.
+__device__ __forceinline__ TileBox tile_box(const SceneK &K, const int org[3], int bmax)
+{
+    TileBox t;
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
+        t.lo[d] = uniform_f((float)max(org[d], 0));
+        t.hi[d] = uniform_f((float)min(org[d] + bmax, K.res - 3));
+    }
+    return t;
+}
+
+// Base cell (as floats) and offset of x; whether the cell is in the box.
+__device__ __forceinline__ bool tile_base(const SceneK &K, const TileBox &t, const float x[3], float fb[3], float f[3])
+{
+    bool in = true;
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
+        const float xi = x[d] * K.inv_dx;
+        fb[d] = floorf(xi - 0.5f);
+        f[d] = xi - fb[d];
+        in &= fb[d] >= t.lo[d] && fb[d] <= t.hi[d];
+    }
+    return in;
+}
+
+// (fb - org) as a linear index of a cube of edge T.
+template <int T>
+__device__ __forceinline__ int tile_index(const float fb[3], const int org[3])
+{
+    const float off = uniform_f((float)(-(org[0] * T + org[1]) * T - org[2]));
+    return (int)fmaf(fb[0], (float)(T * T), fmaf(fb[1], (float)T, fb[2] + off));
 }
 
 __device__ __forceinline__ Material material_of(const SceneDev &S)

@@ -436,17 +436,43 @@ __device__ __forceinline__ void load_particle_xvA(const StepArgs &a, int jj, flo
 // fills the list of substep k + 1; at the end of every substep both are zero.
 __device__ __forceinline__ int *ovf_count(const StepArgs &a, int k) { return a.L.n_ovf + (k & 1); }
 
-// Put a grid block that is not on the static update list on the overflow
-// list (once per substep); n_ovf: the list length of the substep that
-// scatters.
-__device__ __forceinline__ void queue_block(const StepArgs &a, int s, int bin_off, int lb, int *n_ovf)
+// What the scatter paths write, read from the kernel's argument segment where
+// it is needed (the kernels' only argument is their StepArgs): kept live over
+// the particle loops these pointers would push the loops' own scalars out of
+// the scalar registers (each use of a spilled one is a vector instruction).
+struct GridOut {
+    float *gm, *gpx, *gpy, *gpz;
+    unsigned char *touched;
+    int *bflag, *n_ovf, *flags;
+    int2 *ovf;
+    int ovf_cap;
+};
+
+__device__ __forceinline__ GridOut grid_out(int k)
 {
-    int *fl = a.L.bflag + bin_off + lb;
+    typedef const __attribute__((address_space(4))) StepArgs args_t;
+    args_t *p = (args_t *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return {p->gm, p->gpx, p->gpy, p->gpz, p->L.touched, p->L.bflag, p->L.n_ovf + (k & 1), p->flags, p->L.ovf, p->L.ovf_cap};
+}
+
+// Put a grid block that is not on the static update list on the overflow
+// list (once per substep) of the substep that scatters.
+__device__ __forceinline__ void queue_block(const GridOut &o, int s, int bin_off, int lb)
+{
+    int *fl = o.bflag + bin_off + lb;
     if (*fl == 0 && atomicCAS(fl, 0, 1) == 0) {
-        int pos = atomicAdd(n_ovf, 1);
-        if (pos < a.L.ovf_cap) a.L.ovf[pos] = make_int2(s, lb);
-        else atomicOr(a.flags + s, (int)FLAG_OVERFLOW_FULL);
+        int pos = atomicAdd(o.n_ovf, 1);
+        if (pos < o.ovf_cap) o.ovf[pos] = make_int2(s, lb);
+        else atomicOr(o.flags + s, (int)FLAG_OVERFLOW_FULL);
     }
+}
+
+// Quadratic B-spline weight of node o (0, 1, 2) for the offset f in [0.5, 1.5).
+__device__ __forceinline__ float bspline_at(float f, float o)
+{
+    const float u = f - o, e = 1.5f - fabsf(u);
+    return o == 1.0f ? 0.75f - u * u : 0.5f * e * e;
 }
 
 // Slow path of P2G: scatter one particle straight into the global grid and
@@ -458,44 +484,154 @@ __device__ __forceinline__ void queue_block(const StepArgs &a, int s, int bin_of
 // which would otherwise reload it, waiting for every atomic issued so far,
 // before each one.
 template <int B>
-__device__ void p2g_global(const StepArgs &a, int s, const SceneDev &S, const float x[3], const float v[3],
-                           const float A[9], const int b[3], const float f[3], int *n_ovf, int3 home)
+__device__ void p2g_global(const GridOut &o, int s, const SceneDev &S, const float v[3], const float A[9], const int b[3],
+                           const float f[3], int3 home)
 {
     const float mass = uniform_f(S.mass), dx = uniform_f(S.dx);
     const int nb = uniform_i(S.nb), bin_off = uniform_i(S.bin_off);
     const SceneDev Sg = {0, 0, uniform_i(S.res), nb, uniform_ll(S.grid_off)};
-    float w[3][3];
+    // rolled: unrolled, the 27 nodes' temporaries cost the kernels around it their registers
+#pragma unroll 1
+    for (int n = 0; n < 27; n++) {
+        const int q[3] = {n / 9, n / 3 % 3, n % 3};
+        float wt = 1.0f, d[3];
 #pragma unroll
-    for (int d = 0; d < 3; d++) bspline_w(f[d], w[d]);
-#pragma unroll
-    for (int ox = 0; ox < 3; ox++)
-#pragma unroll
-        for (int oy = 0; oy < 3; oy++)
-#pragma unroll
-            for (int oz = 0; oz < 3; oz++) {
-                const float wt = w[0][ox] * w[1][oy] * w[2][oz];
-                const float d[3] = {(ox - f[0]) * dx, (oy - f[1]) * dx, (oz - f[2]) * dx};
-                const long long idx = node_index(Sg, B, b[0] + ox, b[1] + oy, b[2] + oz);
-                atomicAdd(a.gm + idx, wt * mass);
-                atomicAdd(a.gpx + idx, wt * (mass * v[0] + A[0] * d[0] + A[1] * d[1] + A[2] * d[2]));
-                atomicAdd(a.gpy + idx, wt * (mass * v[1] + A[3] * d[0] + A[4] * d[1] + A[5] * d[2]));
-                atomicAdd(a.gpz + idx, wt * (mass * v[2] + A[6] * d[0] + A[7] * d[1] + A[8] * d[2]));
-            }
-#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            wt *= bspline_at(f[k], (float)q[k]);
+            d[k] = ((float)q[k] - f[k]) * dx;
+        }
+        const long long idx = node_index(Sg, B, b[0] + q[0], b[1] + q[1], b[2] + q[2]);
+        atomicAdd(o.gm + idx, wt * mass);
+        atomicAdd(o.gpx + idx, wt * (mass * v[0] + A[0] * d[0] + A[1] * d[1] + A[2] * d[2]));
+        atomicAdd(o.gpy + idx, wt * (mass * v[1] + A[3] * d[0] + A[4] * d[1] + A[5] * d[2]));
+        atomicAdd(o.gpz + idx, wt * (mass * v[2] + A[6] * d[0] + A[7] * d[1] + A[8] * d[2]));
+    }
+#pragma unroll 1
     for (int cx = 0; cx < 2; cx++)
-#pragma unroll
+#pragma unroll 1
         for (int cy = 0; cy < 2; cy++)
-#pragma unroll
+#pragma unroll 1
             for (int cz = 0; cz < 2; cz++) {
                 const int bx = (b[0] + 2 * cx) / B, by = (b[1] + 2 * cy) / B, bz = (b[2] + 2 * cz) / B;
                 if ((cx && bx == b[0] / B) || (cy && by == b[1] / B) || (cz && bz == b[2] / B)) continue;
                 const int lb = (bx * nb + by) * nb + bz;
-                a.L.touched[bin_off + lb] = 1;
+                o.touched[bin_off + lb] = 1;
                 if ((unsigned)(bx - home.x) > 1u || (unsigned)(by - home.y) > 1u || (unsigned)(bz - home.z) > 1u)
-                    queue_block(a, s, bin_off, lb, n_ovf);
+                    queue_block(o, s, bin_off, lb);
             }
 }
 
+
+// Slow lanes of a wave up to this many take the wave-wide slow paths below
+// (about 120 instructions a particle for the scatter and 80 for the gather),
+// more the lane-by-lane ones (950 and 750 instructions for any number of
+// lanes): on the 256-scene workload 0.3 % of the particles change their base
+// cell in a substep and up to 1 % have left their tile before the next
+// re-sort, one or two lanes of every sixth to every second wave.
+constexpr int COOP_LANES = 8;
+
+__device__ __forceinline__ float lane_f(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
+
+// p2g_global for the lanes of `mask`, one particle after the other, its 27
+// nodes on 27 lanes (every lane of the wave must be active).
+template <int B>
+__device__ void p2g_global_wave(const GridOut &o, int s, const SceneDev &S, unsigned long long mask, const float v[3],
+                                const float A[9], const int b[3], const float f[3], int3 home)
+{
+    const float mass = uniform_f(S.mass), dx = uniform_f(S.dx);
+    const int nb = uniform_i(S.nb), bin_off = uniform_i(S.bin_off);
+    const SceneDev Sg = {0, 0, uniform_i(S.res), nb, uniform_ll(S.grid_off)};
+    int lane = threadIdx.x & 63;
+    asm("" : "+v"(lane));   // opaque: what follows from it is formed here, not kept over the particle loop
+    const int ox = lane / 9, oy = lane / 3 % 3, oz = lane % 3;
+    const float of[3] = {(float)ox, (float)oy, (float)oz};
+    while (mask) {
+        const int l = __ffsll(mask) - 1;
+        mask &= mask - 1;
+        int bs[3];
+        float w = 1.0f, d[3];
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            bs[k] = __builtin_amdgcn_readlane(b[k], l);
+            const float fs = lane_f(f[k], l);
+            w *= bspline_at(fs, of[k]);
+            d[k] = (of[k] - fs) * dx;
+        }
+        float p[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+            p[c] = mass * lane_f(v[c], l) + lane_f(A[3 * c], l) * d[0] + lane_f(A[3 * c + 1], l) * d[1] + lane_f(A[3 * c + 2], l) * d[2];
+        if (lane < 27) {
+            const long long idx = node_index(Sg, B, bs[0] + ox, bs[1] + oy, bs[2] + oz);
+            atomicAdd(o.gm + idx, w * mass);
+            atomicAdd(o.gpx + idx, w * p[0]);
+            atomicAdd(o.gpy + idx, w * p[1]);
+            atomicAdd(o.gpz + idx, w * p[2]);
+        }
+        if (lane < 8) {
+            const int cx = lane >> 2, cy = (lane >> 1) & 1, cz = lane & 1;
+            const int bx = (bs[0] + 2 * cx) / B, by = (bs[1] + 2 * cy) / B, bz = (bs[2] + 2 * cz) / B;
+            if (!((cx && bx == bs[0] / B) || (cy && by == bs[1] / B) || (cz && bz == bs[2] / B))) {
+                const int lb = (bx * nb + by) * nb + bz;
+                o.touched[bin_off + lb] = 1;
+                if ((unsigned)(bx - home.x) > 1u || (unsigned)(by - home.y) > 1u || (unsigned)(bz - home.z) > 1u)
+                    queue_block(o, s, bin_off, lb);
+            }
+        }
+    }
+}
+
+// G2P's gather for the lanes of `mask` (particles outside the tile), two
+// particles at a time, their 27 nodes on the two halves of the wave (every
+// lane must be active): vp = sum w v, So[c][e] = sum w v_c o_e.
+template <int B>
+__device__ void gather_wave(const StepArgs &a, const SceneDev &Sn, unsigned long long mask, const int b[3], const float f[3],
+                            float vp[3], float So[3][3])
+{
+    int lane = threadIdx.x & 63;
+    asm("" : "+v"(lane));   // as above
+    const int n = lane & 31;
+    const bool hi = lane >= 32;
+    const int o[3] = {n / 9, n / 3 % 3, n % 3};
+    while (mask) {
+        const int l0 = __ffsll(mask) - 1;
+        mask &= mask - 1;
+        const int l1 = mask ? __ffsll(mask) - 1 : l0;
+        if (mask) mask &= mask - 1;
+        int bs[3];
+        float w = 1.0f;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            bs[k] = (hi ? __builtin_amdgcn_readlane(b[k], l1) : __builtin_amdgcn_readlane(b[k], l0)) + o[k];
+            w *= bspline_at(hi ? lane_f(f[k], l1) : lane_f(f[k], l0), (float)o[k]);
+        }
+        float t[12];
+#pragma unroll
+        for (int q = 0; q < 3; q++) t[q] = 0.0f;
+        if (n < 27) {
+            const long long idx = node_index(Sn, B, bs[0], bs[1], bs[2]);
+            t[0] = w * a.gvx[idx];
+            t[1] = w * a.gvy[idx];
+            t[2] = w * a.gvz[idx];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+#pragma unroll
+            for (int e = 0; e < 3; e++) t[3 + 3 * c + e] = (float)o[e] * t[c];
+#pragma unroll
+        for (int q = 0; q < 12; q++) {
+            float r = t[q];                     // lanes 31 and 63 end with the sums of their halves
+            r = dpp_add<0x111, 0xf>(r);
+            r = dpp_add<0x112, 0xf>(r);
+            r = dpp_add<0x114, 0xf>(r);
+            r = dpp_add<0x118, 0xf>(r);
+            r = dpp_add<0x142, 0xa>(r);
+            const float s0 = lane_f(r, 31), s1 = lane_f(r, 63);
+            float &dst = q < 3 ? vp[q] : So[(q - 3) / 3][(q - 3) % 3];
+            dst = lane == l0 ? s0 : (lane == l1 ? s1 : dst);
+        }
+    }
+}
 
 // Rounding by addition: RND = 1.5 * 2^23, whose float spacing is 1 for sums in [2^23, 2^24).
 constexpr float RND = 12582912.0f;
@@ -515,7 +651,7 @@ constexpr int P2G_COUNT_MIN = 256;
 // the tile while its scatter bound b satisfies b * sp <= lim.
 struct TileScale {
     float msc;   // Sm m: mass-scaled weights
-    float kk;    // Sp / (Sm m): momentum scale relative to the mass-scaled weight
+    float kd, km;   // kk dx and kk m with kk = Sp / (Sm m), the momentum scale relative to the mass-scaled weight
     float sp;    // Sp
     float lim;
     float im, ip;   // 1 / Sm, 1 / Sp
@@ -530,7 +666,9 @@ __device__ __forceinline__ TileScale tile_scale(const SceneK &K, float wsum, flo
     int ep = bmax > 0.0f ? ilogbf(ts.lim / bmax) : 120;
     ep = min(max(ep, -120), 120);
     const float Sm = ldexpf(1.0f, em), Sp = ldexpf(1.0f, ep);
-    ts.kk = Sp / (Sm * K.mass);
+    const float kk = Sp / (Sm * K.mass);
+    ts.kd = uniform_f(kk * K.dx);
+    ts.km = uniform_f(kk * K.mass);
     ts.msc = Sm * K.mass;
     ts.sp = Sp;
     ts.im = 1.0f / Sm;
@@ -541,11 +679,11 @@ __device__ __forceinline__ TileScale tile_scale(const SceneK &K, float wsum, flo
 // One particle's 27 stencil terms into the tile t64 (per node two 64-bit sums,
 // (p_x, m) and (p_y, p_z) as (hi, lo), each the exact sum of 32-bit fixed-point
 // terms packed as hi * 2^32 + lo: an integer sum, so both halves are recovered
-// exactly while they fit in 32 bits); tb: the particle's base cell in tile
-// coordinates, f its offset from it in cells.
+// exactly while they fit in 32 bits); tb0: the sums of the particle's base
+// cell, f its offset from it in cells.
 template <int B>
-__device__ __forceinline__ void scatter_packed(long long *t64, const int tb[3], const float f[3], const TileScale &ts,
-                                               const SceneK &K, const float v[3], const float A[9])
+__device__ __forceinline__ void scatter_packed(long long *tb0, const float f[3], const TileScale &ts, const float v[3],
+                                               const float A[9])
 {
     constexpr int T = tile_edge<B>(), T3 = T * T * T;
     float wx[3], wy[3], wz[3];
@@ -559,10 +697,9 @@ __device__ __forceinline__ void scatter_packed(long long *t64, const int tb[3], 
 #pragma unroll
     for (int c = 0; c < 3; c++) {
 #pragma unroll
-        for (int e = 0; e < 3; e++) Ad[c][e] = ts.kk * A[3 * c + e] * K.dx;
-        r0[c] = ts.kk * K.mass * v[c] - (Ad[c][0] * f[0] + Ad[c][1] * f[1] + Ad[c][2] * f[2]);
+        for (int e = 0; e < 3; e++) Ad[c][e] = ts.kd * A[3 * c + e];
+        r0[c] = ts.km * v[c] - (Ad[c][0] * f[0] + Ad[c][1] * f[1] + Ad[c][2] * f[2]);
     }
-    long long *tb0 = t64 + (tb[0] * T + tb[1]) * T + tb[2];
     // r at offset (ox, oy, oz): r0 + ox Ad_x + oy Ad_y + oz Ad_z, one add per axis step
     // (offset 0 adds nothing, 1 adds Ad, 2 adds 2 Ad)
     auto step = [](float r, float d, int o) { return o == 0 ? r : (o == 1 ? r + d : fmaf(2.0f, d, r)); };
@@ -594,8 +731,8 @@ __device__ __forceinline__ void scatter_packed(long long *t64, const int tb[3], 
 // The tile's node sums into the global grid: marks the grid blocks that
 // received mass, queues lower neighbour blocks off the update list.
 template <int B, int NT>
-__device__ void flush_packed(const StepArgs &a, int s, const SceneDev &S, const int org[3], const long long *t64,
-                             const TileScale &ts, int *n_ovf)
+__device__ void flush_packed(const GridOut &o, int s, const SceneDev &S, const int org[3], const long long *t64,
+                             const TileScale &ts)
 {
     constexpr int T = tile_edge<B>(), T3 = T * T * T;
     const int home[3] = {(org[0] + 1) / B, (org[1] + 1) / B, (org[2] + 1) / B};
@@ -616,20 +753,20 @@ __device__ void flush_packed(const StepArgs &a, int s, const SceneDev &S, const 
         int gi = org[0] + tx, gj = org[1] + ty, gk = org[2] + tz;
         if (gi < 0 || gj < 0 || gk < 0 || gi >= res || gj >= res || gk >= res) continue;
         const int lb = ((gi / B) * nb + (gj / B)) * nb + (gk / B);
-        a.L.touched[bin_off + lb] = 1;
+        o.touched[bin_off + lb] = 1;
         if (tx == 0 || ty == 0 || tz == 0)
             lower |= 1u << (((gi / B - home[0] + 1) * 3 + (gj / B - home[1] + 1)) * 3 + (gk / B - home[2] + 1));
         const long long idx = node_index(Sg, B, gi, gj, gk);
-        atomicAdd(a.gm + idx, (float)m0 * ts.im);
-        atomicAdd(a.gpx + idx, (float)p0 * ts.ip);
-        atomicAdd(a.gpy + idx, (float)p1 * ts.ip);
-        atomicAdd(a.gpz + idx, (float)p2 * ts.ip);
+        atomicAdd(o.gm + idx, (float)m0 * ts.im);
+        atomicAdd(o.gpx + idx, (float)p0 * ts.ip);
+        atomicAdd(o.gpy + idx, (float)p1 * ts.ip);
+        atomicAdd(o.gpz + idx, (float)p2 * ts.ip);
     }
     lower = wave_or(lower);
     const int lane = threadIdx.x & 63;
     if (lane < 27 && ((lower >> lane) & 1u)) {
         const int lb = ((home[0] - 1 + lane / 9) * nb + (home[1] - 1 + (lane / 3) % 3)) * nb + (home[2] - 1 + lane % 3);
-        queue_block(a, s, bin_off, lb, n_ovf);
+        queue_block(o, s, bin_off, lb);
     }
 }
 
@@ -645,6 +782,7 @@ __device__ void p2g_item(const StepArgs &a, int it, const Item &item, int *tile,
     const int org[3] = {bx * B - 1, by * B - 1, bz * B - 1};
     const int3 home = make_int3(bx, by, bz);
     const SceneK K = scene_k(S);
+    const TileBox box = tile_box(K, org, tile_bmax<B>());
     // largest particle count of a base cell, left by the G2P that moved the
     // particles (0 after a re-sort or a surrogate step: count here)
     const int known = item.count > P2G_COUNT_MIN ? a.L.icell[it] : 0;
@@ -652,7 +790,7 @@ __device__ void p2g_item(const StepArgs &a, int it, const Item &item, int *tile,
 
     // the first particle's state is in flight while the tile is cleared; the
     // next one's is loaded while the current one scatters
-    float xn[3], vn[3], An[9];
+    float xn[3] = {}, vn[3] = {}, An[9] = {};
     if (t < item.count) load_particle_xvA(a, item.start + t, xn, vn, An);
     // LDS tile: per node two 64-bit sums, (p_x, m) and (p_y, p_z) as (hi, lo),
     // each the exact sum of 32-bit fixed-point terms packed as hi * 2^32 + lo
@@ -680,17 +818,10 @@ __device__ void p2g_item(const StepArgs &a, int it, const Item &item, int *tile,
             const int li = base + t;
             if (li >= item.count) break;
             const unsigned jo = (unsigned)(item.start + li) << 2;
-            int cl = 0, in = 1, c = 0;
+            float x[3], fb[3], f[3];
 #pragma unroll
-            for (int d = 0; d < 3; d++) {
-                int bp;
-                float f;
-                particle_base(K, pload(a.P, a.pstride, X0 + d, jo), bp, f, cl);
-                const int tb = bp - org[d];
-                in &= (tb >= 0) & (tb <= tile_bmax<B>());
-                c = c * (tile_bmax<B>() + 1) + tb;
-            }
-            if (in && !cl) atomicAdd(cells + c, 1);
+            for (int d = 0; d < 3; d++) x[d] = pload(a.P, a.pstride, X0 + d, jo);
+            if (tile_base(K, box, x, fb, f)) atomicAdd(cells + tile_index<tile_bmax<B>() + 1>(fb, org), 1);
         }
         __syncthreads();
         int mx = 0;
@@ -706,8 +837,11 @@ __device__ void p2g_item(const StepArgs &a, int it, const Item &item, int *tile,
 
     const TileScale ts = tile_scale(K, wsum, bmax);
 
-    for (int li = t; li < item.count; li += NT) {
-        float x[3], v[3], A[9], f[3];
+    const int lane = t & 63;
+    for (int k0 = t - lane; k0 < item.count; k0 += NT) {   // wave-uniform: the wave's next 64 particles
+        const int li = k0 + lane;
+        const bool act = li < item.count;
+        float x[3], v[3], A[9], fb[3], f[3];
 #pragma unroll
         for (int d = 0; d < 3; d++) {
             x[d] = xn[d];
@@ -716,24 +850,25 @@ __device__ void p2g_item(const StepArgs &a, int it, const Item &item, int *tile,
 #pragma unroll
         for (int e = 0; e < 9; e++) A[e] = An[e];
         if (li + NT < item.count) load_particle_xvA(a, item.start + li + NT, xn, vn, An);
-        int bp[3];
-        int cl = 0, in = 1;
+        const bool in = tile_base(K, box, x, fb, f);
+        const unsigned long long slow = __ballot(act && !in);
+        if (slow) {
+            int bp[3] = {0, 0, 0}, cl = 0;
+            float fp[3] = {0.0f, 0.0f, 0.0f};
+            if (act && !in) {
 #pragma unroll
-        for (int d = 0; d < 3; d++) {
-            particle_base(K, x[d], bp[d], f[d], cl);
-            int tb = bp[d] - org[d];
-            in &= (tb >= 0) & (tb <= tile_bmax<B>());
+                for (int d = 0; d < 3; d++) particle_base(K, x[d], bp[d], fp[d], cl);
+                if (cl) atomicOr(a.flags + s, (int)FLAG_CLAMPED);
+            }
+            const GridOut o = grid_out(a.substep);
+            if (__popcll(slow) <= COOP_LANES) p2g_global_wave<B>(o, s, S, slow, v, A, bp, fp, home);
+            else if (act && !in) p2g_global<B>(o, s, S, v, A, bp, fp, home);
         }
-        if (cl) atomicOr(a.flags + s, (int)FLAG_CLAMPED);
-        if (!in || cl) {
-            p2g_global<B>(a, s, S, x, v, A, bp, f, ovf_count(a, a.substep), home);
-            continue;
-        }
-        const int tb[3] = {bp[0] - org[0], bp[1] - org[1], bp[2] - org[2]};
-        scatter_packed<B>(t64, tb, f, ts, K, v, A);
+        if (act && in) scatter_packed<B>(t64 + tile_index<T>(fb, org), f, ts, v, A);
     }
+    const GridOut go = grid_out(a.substep);
     __syncthreads();
-    flush_packed<B, NT>(a, s, S, org, t64, ts, ovf_count(a, a.substep));
+    flush_packed<B, NT>(go, s, S, org, t64, ts);
     __syncthreads();
 }
 
@@ -932,6 +1067,7 @@ __device__ void g2p_item(const StepArgs &a, int it, const Item &item, float *vt,
     // the compiler, which would reload them after each one)
     const Material mat = material_of(S);
     const SceneK K = scene_k(S);
+    const TileBox box = tile_box(K, org, tile_bmax<B>());
     const SceneDev Sn = {0, 0, K.res, uniform_i(S.nb), uniform_ll(S.grid_off)};   // for node_index
     TileScale ts{};
     if (FUSE) {
@@ -982,6 +1118,7 @@ __device__ void g2p_item(const StepArgs &a, int it, const Item &item, float *vt,
     for (int k0 = t - lane; k0 < item.count; k0 += NT) {
         const int li = k0 + lane;
         const unsigned jo = (unsigned)(item.start + li) << 2;
+        float *const P = a.P;
         float x[3], G[9];
         if (PF) {
 #pragma unroll
@@ -990,36 +1127,41 @@ __device__ void g2p_item(const StepArgs &a, int it, const Item &item, float *vt,
             for (int e = 0; e < 9; e++) G[e] = pw[(3 + e) * 64 + lane];
             wait_lds();
             // the next batch streams into LDS while this one computes
-            pf_issue(a.P, ps, item.start + k0 + NT, item.count - (k0 + NT), lane, pw);
+            pf_issue(P, ps, item.start + k0 + NT, item.count - (k0 + NT), lane, pw);
         }
-        if (li >= item.count) {
-            if (PF) wait_vmem();
-            continue;
-        }
-        if (!PF) {
+        const bool act = li < item.count;
+        if (!PF && act) {
 #pragma unroll
-            for (int d = 0; d < 3; d++) x[d] = pload(a.P, ps, X0 + d, jo);
+            for (int d = 0; d < 3; d++) x[d] = pload(P, ps, X0 + d, jo);
 #pragma unroll
-            for (int e = 0; e < 9; e++) G[e] = pload(a.P, ps, G00 + e, jo);
+            for (int e = 0; e < 9; e++) G[e] = pload(P, ps, G00 + e, jo);
         }
-        int b[3], cl = 0, in = 1;
-        float f[3];
+        float fb[3], f[3], vp[3] = {0.0f, 0.0f, 0.0f};
+        float So[3][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};   // sum w v_c o_e
+        const bool in = tile_base(K, box, x, fb, f);
+        const unsigned long long out = __ballot(act && !in);
+        const bool coop = __popcll(out) <= COOP_LANES;
+        int b[3] = {0, 0, 0};
+        if (out) {
+            // outside the tile (drifted since the re-sort): the nodes straight from the grid
+            if (act && !in) {
+                int cl = 0;
 #pragma unroll
-        for (int d = 0; d < 3; d++) {
-            particle_base(K, x[d], b[d], f[d], cl);
-            int tb = b[d] - org[d];
-            in &= (tb >= 0) & (tb <= tile_bmax<B>());
+                for (int d = 0; d < 3; d++) particle_base(K, x[d], b[d], f[d], cl);
+                cl_any |= cl;
+            }
+            if (coop) gather_wave<B>(a, Sn, out, b, f, vp, So);
         }
-        cl_any |= cl;
+        bool slow = false;          // scattered by the slow path below
+        float fn[3], An[9];
+        if (act) {
         float wx[3], wy[3], wz[3];
         bspline_w(f[0], wx);
         bspline_w(f[1], wy);
         bspline_w(f[2], wz);
-        float vp[3] = {0.0f, 0.0f, 0.0f};
-        float So[3][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};   // sum w v_c o_e
         if (in) {
             // separable gather: reduce over z, then y, then x
-            const float *vb = vt + ((b[0] - org[0]) * T + (b[1] - org[1])) * T + (b[2] - org[2]);
+            const float *vb = vt + tile_index<T>(fb, org);
             const float wz2 = 2.0f * wz[2], wy2 = 2.0f * wy[2], wx2 = 2.0f * wx[2];
 #pragma unroll
             for (int ox = 0; ox < 3; ox++) {
@@ -1047,26 +1189,27 @@ __device__ void g2p_item(const StepArgs &a, int it, const Item &item, float *vt,
                     So[c][2] = fmaf(wx[ox], Bz[c], So[c][2]);
                 }
             }
-        } else {
-            // outside the tile (drifted since the re-sort): the nodes straight from the grid, nine
-            // at a time in flight, with the scene constants in registers (the particle stores may
+        } else if (!coop) {
+            // the nodes straight from the grid, with the scene constants in registers (the particle stores may
             // alias the scene record for the compiler, which would reload it and wait for them)
-            for (int ox = 0; ox < 3; ox++) {
-                float g[9][3];
+#pragma unroll 1
+            for (int q = 0; q < 9; q++) {
+                const int ox = q / 3, oy = q % 3;
+                float g[3][3];
 #pragma unroll
-                for (int q = 0; q < 9; q++) {
-                    const long long idx = node_index(Sn, B, b[0] + ox, b[1] + q / 3, b[2] + q % 3);
-                    g[q][0] = a.gvx[idx];
-                    g[q][1] = a.gvy[idx];
-                    g[q][2] = a.gvz[idx];
+                for (int oz = 0; oz < 3; oz++) {
+                    const long long idx = node_index(Sn, B, b[0] + ox, b[1] + oy, b[2] + oz);
+                    g[oz][0] = a.gvx[idx];
+                    g[oz][1] = a.gvy[idx];
+                    g[oz][2] = a.gvz[idx];
                 }
+                const float wxy = bspline_at(f[0], (float)ox) * bspline_at(f[1], (float)oy);
 #pragma unroll
-                for (int q = 0; q < 9; q++) {
-                    const int oy = q / 3, oz = q % 3;
-                    const float w = wx[ox] * wy[oy] * wz[oz];
+                for (int oz = 0; oz < 3; oz++) {
+                    const float w = wxy * wz[oz];
 #pragma unroll
                     for (int c = 0; c < 3; c++) {
-                        const float tv = w * g[q][c];
+                        const float tv = w * g[oz][c];
                         vp[c] += tv;
                         So[c][0] += (float)ox * tv;
                         So[c][1] += (float)oy * tv;
@@ -1084,20 +1227,12 @@ __device__ void g2p_item(const StepArgs &a, int it, const Item &item, float *vt,
             for (int e = 0; e < 3; e++) C[3 * c + e] = Dd * fmaf(-vp[c], f[e], So[c][e]);
 #pragma unroll
         for (int d = 0; d < 3; d++) x[d] = fmaf(K.dt, vp[d], x[d]);
-        // base cell of the new position in this item's P2G tile
-        int bn[3], tbn[3], inn = 1, cln = 0;
-        float fn[3];
-        {
-            int c = 0;
-#pragma unroll
-            for (int d = 0; d < 3; d++) {
-                particle_base(K, x[d], bn[d], fn[d], cln);
-                tbn[d] = bn[d] - org[d];
-                inn &= (tbn[d] >= 0) & (tbn[d] <= tile_bmax<B>());
-                c = c * (tile_bmax<B>() + 1) + tbn[d];
-            }
-            if (inn && !cln) atomicAdd(cells + c, 1);
-        }
+        // base cell of the new position in this item's P2G tile: the same one as before for all but
+        // a few particles of a substep
+        float fbn[3];
+        const bool inn = tile_base(K, box, x, fbn, fn);
+        const bool kept = in && fbn[0] == fb[0] && fbn[1] == fb[1] && fbn[2] == fb[2];
+        if (inn) atomicAdd(cells + tile_index<tile_bmax<B>() + 1>(fbn, org), 1);
         if (PEN) {
             // inside collider c at the new position: v += -phi n / (4 dt), a spring of stiffness
             // m / (4 dt^2) along the outward normal (the stored v, hence the next scatter bound,
@@ -1151,30 +1286,44 @@ __device__ void g2p_item(const StepArgs &a, int it, const Item &item, float *vt,
         bad |= !(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]));
         bad_any |= bad;
         // the prefetch has had the whole computation to land; waiting here (not at
-        // the top of the next batch) keeps the wait off this batch's stores
+        // the top of the next batch) keeps the wait off this batch's stores (lane 0 of a wave is
+        // active in every batch, so the wave always waits)
         if (PF) wait_vmem();
 #pragma unroll
         for (int d = 0; d < 3; d++) {
-            pstore(a.P, ps, X0 + d, jo, x[d]);
-            if (!FUSE) pstore(a.P, ps, V0 + d, jo, vp[d]);
+            pstore(P, ps, X0 + d, jo, x[d]);
+            if (!FUSE) pstore(P, ps, V0 + d, jo, vp[d]);
         }
-        float An[9];
 #pragma unroll
         for (int e = 0; e < 9; e++) {
             An[e] = fmaf(K.mass, C[e], -K.kstress * tau[e]);
-            if (!FUSE) pstore(a.P, ps, A00 + e, jo, An[e]);
-            pstore(a.P, ps, G00 + e, jo, Gn[e]);
+            if (!FUSE) pstore(P, ps, A00 + e, jo, An[e]);
+            pstore(P, ps, G00 + e, jo, Gn[e]);
         }
         // a non-finite v or A (the next P2G would scatter it as garbage)
         const float sb = scatter_bound(K.mass, K.dx, vp, An);
         bad_any |= !(sb <= 3.0e38f);
         bnd = fmaxf(bnd, sb);
         if (FUSE) {
-            const bool kept = bn[0] == b[0] && bn[1] == b[1] && bn[2] == b[2];
-            if (inn && !cln && kept && sb * ts.sp <= ts.lim) scatter_packed<B>(t64, tbn, fn, ts, K, vp, An);
-            else p2g_global<B>(a, s, S, x, vp, An, bn, fn, ovf_count(a, a.substep + 1), home);
+            slow = !(kept && sb * ts.sp <= ts.lim);
+        }
+        }   // act
+        if (FUSE) {
+            const unsigned long long sm = __ballot(slow);
+            if (sm) {
+                int bn[3] = {0, 0, 0}, cln = 0;
+                float fs[3] = {0.0f, 0.0f, 0.0f};
+                if (slow)
+#pragma unroll
+                    for (int d = 0; d < 3; d++) particle_base(K, x[d], bn[d], fs[d], cln);
+                const GridOut o = grid_out(a.substep + 1);
+                if (__popcll(sm) <= COOP_LANES) p2g_global_wave<B>(o, s, S, sm, vp, An, bn, fs, home);
+                else if (slow) p2g_global<B>(o, s, S, vp, An, bn, fs, home);
+            }
+            if (act && !slow) scatter_packed<B>(t64 + tile_index<T>(fb, org), fn, ts, vp, An);
         }
     }
+    const GridOut go = grid_out(a.substep + 1);   // on its way while the wave finishes
     bnd = wave_max(bnd);
     if ((t & 63) == 0 && bnd > 0.0f) atomicMax((int *)(a.L.ibound + it), __float_as_int(bnd));
     if (PEN && a.wrench) {
@@ -1195,7 +1344,7 @@ __device__ void g2p_item(const StepArgs &a, int it, const Item &item, float *vt,
     if (bad_any) atomicOr(a.flags + s, (int)FLAG_NONFINITE);
     if (cl_any) atomicOr(a.flags + s, (int)FLAG_CLAMPED);
     __syncthreads();
-    if (FUSE) flush_packed<B, NT>(a, s, S, org, t64, ts, ovf_count(a, a.substep + 1));
+    if (FUSE) flush_packed<B, NT>(go, s, S, org, t64, ts);
     int mx = 0;
     for (int n = t; n < NC; n += NT) mx = max(mx, cells[n]);
     mx = wave_max_i(mx);
@@ -1231,6 +1380,11 @@ __global__ __launch_bounds__(NT, 4) void k_g2p(StepArgs a)
 // CU (measured 2.5 % slower on the 256-scene workload, 1.6 % on the heap).
 // With penalty contact the kernel needs more registers than four workgroups
 // leave, and keeps the prefetch.
+// Bound by vector instructions (83 to 87 % of the cycles issue one at 256
+// scenes): what it gained came from fewer of them, the strain series in scalar
+// invariants and the wave-wide slow paths (100 substeps of 256 scenes of
+// 8,000 particles 44.1 -> 40.5 ms, of 23 scenes 2.84 -> 2.52 ms with the same
+// changes in the separate kernels).
 template <int B, bool PEN, int NT>
 __global__ __launch_bounds__(NT, 4) void k_g2p2g(StepArgs a)
 {
