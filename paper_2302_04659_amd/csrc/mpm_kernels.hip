@@ -692,13 +692,19 @@ __device__ __forceinline__ void scatter_packed(long long *tb0, const float f[3],
     bspline_w(f[2], wz);
 #pragma unroll
     for (int o = 0; o < 3; o++) wx[o] *= ts.msc;
-    // r(o) = kk * (m v + A (o - f) dx); increments along each axis
+    // r(o) = kk * (m v + A (o - f) dx); increments along each axis.  The roundings are written out (the
+    // increments rounded before they are added, the order of the fused sum): left to the compiler they
+    // follow the code around this function, and a last bit that turns here is 1e-3 of a network output
+    // whose inputs are rounded to BF16
     float Ad[3][3], r0[3];
 #pragma unroll
     for (int c = 0; c < 3; c++) {
 #pragma unroll
-        for (int e = 0; e < 3; e++) Ad[c][e] = ts.kd * A[3 * c + e];
-        r0[c] = ts.km * v[c] - (Ad[c][0] * f[0] + Ad[c][1] * f[1] + Ad[c][2] * f[2]);
+        for (int e = 0; e < 3; e++) {
+#pragma clang fp contract(off)
+            Ad[c][e] = ts.kd * A[3 * c + e];
+        }
+        r0[c] = fmaf(ts.km, v[c], -fmaf(Ad[c][2], f[2], fmaf(Ad[c][0], f[0], Ad[c][1] * f[1])));
     }
     // r at offset (ox, oy, oz): r0 + ox Ad_x + oy Ad_y + oz Ad_z, one add per axis step
     // (offset 0 adds nothing, 1 adds Ad, 2 adds 2 Ad)
@@ -1281,7 +1287,7 @@ __device__ void g2p_item(const StepArgs &a, int it, const Item &item, float *vt,
         } else if (mat.model == 2) {
             fluid_update(Gt, mat, Gn, tau, bad);
         } else {
-            hencky_update(Gt, mat, Gn, tau, bad);
+            hencky_update<!FUSE>(Gt, mat, Gn, tau, bad);
         }
         bad |= !(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]));
         bad_any |= bad;

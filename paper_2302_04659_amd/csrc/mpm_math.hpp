@@ -368,29 +368,78 @@ MPM_HD void sym_mul(const float a[6], const float b[6], float c[6])
 // ln b = 2 atanh(Z) with Z = (b - I)(b + I)^-1 (functions of b, so they
 // commute), hence e = Z + Z^3/3 + Z^5/5 + Z^7/7 + Z^9/9 + ...; while
 // |b - I|_F <= 0.35 the eigenvalues of Z stay within 0.35 / 1.65 and the first
-// term left out is below 4e-9.  By the theorem of Cayley and Hamilton every
-// function of s = b - I is a s^2 + b s + c I with scalars from its invariants,
-// so the series, the inverse and Z^2 are scalar work and only s^2 is a matrix
-// product (the substep is bound by its vector instructions; the same series in
-// matrix products took 40 more).  The deviatoric norm of e is that of the
+// term left out is below 4e-9.  The deviatoric norm of e is that of the
 // principal log strains, so the yield test is the eigen path's.
-// WIDE: states up to |b - I|_F <= 0.6 take the terms to Z^17 (24 scalar
-// operations more against the eigen path's 770; eigenvalues of Z within
-// 0.6 / 1.4, the first term left out below 2e-8 of e), on the GPU when a lane
-// of the wave needs them.
-// hencky_series_strain: e (symmetric, as sym_mul's six entries) and 1 when
-// the series applies (det F > 1/2, |b - I|_F <= 0.35 or 0.6, no yield), else 0.
-template <bool WIDE = false>
-MPM_HD int hencky_series_strain(const float *G, const Material &mat, float e[6])
+// Two forms of the series, e (symmetric, as sym_mul's six entries) and 1 when
+// it applies (det F > 1/2, |b - I|_F in its range, no yield), else 0:
+// hencky_series_strain in matrix products, for every stress that is stored or
+// has to undo a stored one (the affine momentum A = m C - k tau(F) keeps C to
+// the last bits only if one function forms tau on both sides);
+// hencky_invariant_strain for the fused launches, which keep A in registers
+// and are bound by their vector instructions.
+
+// s = b - I = G + G^T + G G^T
+MPM_HD void left_strain(const float *G, float s[6])
 {
-    // s = b - I = G + G^T + G G^T
-    float s[6], s2[6];
     s[0] = 2.0f * G[0] + (G[0] * G[0] + G[1] * G[1] + G[2] * G[2]);
     s[1] = 2.0f * G[4] + (G[3] * G[3] + G[4] * G[4] + G[5] * G[5]);
     s[2] = 2.0f * G[8] + (G[6] * G[6] + G[7] * G[7] + G[8] * G[8]);
     s[3] = G[1] + G[3] + (G[0] * G[3] + G[1] * G[4] + G[2] * G[5]);
     s[4] = G[2] + G[6] + (G[0] * G[6] + G[1] * G[7] + G[2] * G[8]);
     s[5] = G[5] + G[7] + (G[3] * G[6] + G[4] * G[7] + G[5] * G[8]);
+}
+
+MPM_HD int hencky_series_strain(const float *G, const Material &mat, float e[6])
+{
+    float s[6];
+    left_strain(G, s);
+    const float nb2 = s[0] * s[0] + s[1] * s[1] + s[2] * s[2] + 2.0f * (s[3] * s[3] + s[4] * s[4] + s[5] * s[5]);
+    // (b + I)^-1 = (2 I + s)^-1 by its adjugate
+    const float a = 2.0f + s[0], d = 2.0f + s[1], f = 2.0f + s[2];
+    float inv[6];
+    inv[0] = d * f - s[5] * s[5];
+    inv[1] = a * f - s[4] * s[4];
+    inv[2] = a * d - s[3] * s[3];
+    inv[3] = s[4] * s[5] - s[3] * f;
+    inv[4] = s[3] * s[5] - s[4] * d;
+    inv[5] = s[3] * s[4] - a * s[5];
+    const float idet = frcp(a * inv[0] + s[3] * inv[3] + s[4] * inv[4]);
+#pragma unroll
+    for (int k = 0; k < 6; k++) inv[k] *= idet;
+    float z[6], z2[6], p[6], q[6];
+    sym_mul(s, inv, z);
+    sym_mul(z, z, z2);
+    // p = I + z2/3 + z2^2/5 + z2^3/7 + z2^4/9 (Horner in z2)
+#pragma unroll
+    for (int k = 0; k < 6; k++) p[k] = z2[k] * (1.0f / 9.0f) + (k < 3 ? 1.0f / 7.0f : 0.0f);
+    sym_mul(z2, p, q);
+#pragma unroll
+    for (int k = 0; k < 6; k++) p[k] = q[k] + (k < 3 ? 1.0f / 5.0f : 0.0f);
+    sym_mul(z2, p, q);
+#pragma unroll
+    for (int k = 0; k < 6; k++) p[k] = q[k] + (k < 3 ? 1.0f / 3.0f : 0.0f);
+    sym_mul(z2, p, q);
+#pragma unroll
+    for (int k = 0; k < 6; k++) p[k] = q[k] + (k < 3 ? 1.0f : 0.0f);
+    sym_mul(z, p, e);
+    const float mean = (e[0] + e[1] + e[2]) * (1.0f / 3.0f);
+    const float d0 = e[0] - mean, d1 = e[1] - mean, d2 = e[2] - mean;
+    const float nd2 = d0 * d0 + d1 * d1 + d2 * d2 + 2.0f * (e[3] * e[3] + e[4] * e[4] + e[5] * e[5]);
+    return nb2 <= 0.1225f && det_minus_one(G) > -0.5f && !(mat.plastic && nd2 > mat.yield_eps * mat.yield_eps);
+}
+
+// By the theorem of Cayley and Hamilton every function of s = b - I is
+// a s^2 + b s + c I with scalars from its invariants, so the series, the inverse
+// and Z^2 are scalar work and only s^2 is a matrix product (40 vector
+// instructions fewer than the matrix form, and a smaller error: rms 8.9e-8
+// against 1.24e-7 of e at strains of 0.01).  States up to |b - I|_F <= 0.6 take
+// the terms to Z^17 (24 scalar operations more against the eigen path's 770;
+// eigenvalues of Z within 0.6 / 1.4, the first term left out below 2e-8 of e),
+// on the GPU when a lane of the wave needs them.
+MPM_HD int hencky_invariant_strain(const float *G, const Material &mat, float e[6])
+{
+    float s[6], s2[6];
+    left_strain(G, s);
     sym_mul(s, s, s2);
     // invariants of s; tr s^2 = |b - I|_F^2
     const float nb2 = s2[0] + s2[1] + s2[2];
@@ -410,11 +459,11 @@ MPM_HD int hencky_series_strain(const float *G, const Material &mat, float e[6])
         pc = pa * i3;
         pa = t;
     };
-    bool wide = WIDE && nb2 > 0.1225f;
+    bool wide = nb2 > 0.1225f;
 #if defined(__HIP_DEVICE_COMPILE__)
-    if (WIDE) wide = __ballot(wide) != 0;
+    wide = __ballot(wide) != 0;
 #endif
-    if (WIDE && wide) {
+    if (wide) {
         pa = i1 * (1.0f / 17.0f);
         pb = fmaf(i2, -1.0f / 17.0f, 1.0f / 15.0f);
         pc = i3 * (1.0f / 17.0f);
@@ -455,7 +504,7 @@ MPM_HD int hencky_series_strain(const float *G, const Material &mat, float e[6])
     const float mean = (e[0] + e[1] + e[2]) * (1.0f / 3.0f);
     const float d0 = e[0] - mean, d1 = e[1] - mean, d2 = e[2] - mean;
     const float nd2 = d0 * d0 + d1 * d1 + d2 * d2 + 2.0f * (e[3] * e[3] + e[4] * e[4] + e[5] * e[5]);
-    return nb2 <= (WIDE ? 0.36f : 0.1225f) && det_minus_one(G) > -0.5f && !(mat.plastic && nd2 > mat.yield_eps * mat.yield_eps);
+    return nb2 <= 0.36f && det_minus_one(G) > -0.5f && !(mat.plastic && nd2 > mat.yield_eps * mat.yield_eps);
 }
 
 // tau = 2 mu e + lambda tr(e) I.
@@ -487,11 +536,13 @@ MPM_HD int hencky_elastic_series(const float *G, const Material &mat, float *Gou
 // Returns 1 if the particle yielded.  States near the identity that stay
 // elastic take the series above, on the GPU when every lane of the wave
 // qualifies (one path per wave); the rest the eigen-decomposition of F^T F.
+// STORED: the stress goes into, or undoes, a stored A.
+template <bool STORED = false>
 MPM_HD int hencky_update(const float *Gt, const Material &mat, float *Gout, float tau[9], int &bad)
 {
 #if MPM_HENCKY_SERIES
     float e[6];
-    int ok = hencky_series_strain<true>(Gt, mat, e);
+    int ok = STORED ? hencky_series_strain(Gt, mat, e) : hencky_invariant_strain(Gt, mat, e);
 #if defined(__HIP_DEVICE_COMPILE__)
     ok = __ballot(ok) == __ballot(1);
 #endif
@@ -552,7 +603,7 @@ MPM_HD void stress_of(const float *G, const Material &mat, float tau[9], int &ba
     Material m2 = mat;
     m2.plastic = 0;
     float Gc[9];
-    hencky_update(G, m2, Gc, tau, bad);
+    hencky_update<true>(G, m2, Gc, tau, bad);
 }
 
 // ---------------------------------------------------------------- rotations and SDFs

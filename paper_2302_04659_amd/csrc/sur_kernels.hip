@@ -283,7 +283,7 @@ __device__ void sur_advance_item(const StepArgs &a, int it, const Item &item, fl
         } else if (mat.model == 2) {
             fluid_update(Gt, mat, Gn, tau, bad);
         } else {
-            hencky_update(Gt, mat, Gn, tau, bad);
+            hencky_update<true>(Gt, mat, Gn, tau, bad);
         }
         bad |= !(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]));
         bad_any |= bad;
