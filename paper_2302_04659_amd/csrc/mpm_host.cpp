@@ -348,6 +348,17 @@ hipError_t resolve_timing(mpm_ctx ctx)
     return hipSuccess;
 }
 
+// Particles per work item, MPM_OPT_CHUNK at most.  A context too small to give
+// every CU a chunk of that size cuts its blocks finer, to about one item per CU
+// and a whole wave at least: the particle kernels last as long as the longest
+// item, and the tile each further item stages and flushes runs on idle CUs.
+int chunk_of(mpm_ctx ctx)
+{
+    if (ctx->persistent) return ctx->CH;   // its grid barriers cost per workgroup
+    const long long per_cu = ((long long)ctx->N + ctx->cus - 1) / ctx->cus;
+    return (int)std::min<long long>(ctx->CH, std::max<long long>((per_cu + 63) / 64 * 64, 64));
+}
+
 SortArgs sort_args(mpm_ctx ctx)
 {
     SortArgs a{};
@@ -369,7 +380,7 @@ SortArgs sort_args(mpm_ctx ctx)
     a.dil = ctx->d_dil;
     a.L = ctx->L;
     a.B = ctx->B;
-    a.CH = ctx->CH;
+    a.CH = chunk_of(ctx);
     return a;
 }
 
