@@ -114,11 +114,23 @@ __global__ __launch_bounds__(WG) void k_dilate(SortArgs a)
 static constexpr int SCAN_PER = 8;
 static constexpr int SCAN_TILE = WG * SCAN_PER;
 
+// Particles per item of a block with c of them.  Blocks are cut to a.cut, but
+// not where they hold over 12 particles a cell: there the largest sum a node of
+// the item can reach sets the P2G's fixed-point scale, a shorter item would get
+// a finer one, and the rounding of its terms would follow the launch
+// configuration (6,000 fluid particles at 40 a cell: velocity gradients moved by
+// 2e-5).  Up to there the limit of the single term sets the scale, whatever the
+// item's length.
+__device__ __forceinline__ int item_size(const SortArgs &a, int c)
+{
+    return c <= 12 * a.B * a.B * a.B ? a.cut : a.CH;
+}
+
 __device__ __forceinline__ int3 bin_triple(const SortArgs &a, int b)
 {
     if (b >= a.T) return make_int3(0, 0, 0);
-    int c = a.count[b];
-    return make_int3(c, (c + a.CH - 1) / a.CH, (int)a.dil[b]);
+    const int c = a.count[b], ch = item_size(a, c);
+    return make_int3(c, (c + ch - 1) / ch, (int)a.dil[b]);
 }
 
 __device__ __forceinline__ int3 add3(int3 x, int3 y) { return make_int3(x.x + y.x, x.y + y.y, x.z + y.z); }
@@ -204,12 +216,13 @@ __global__ __launch_bounds__(WG) void k_scan_emit(SortArgs a)
                 uint32_t m = (uint32_t)(b - off);
                 int bx = compact3(m), by = compact3(m >> 1), bz = compact3(m >> 2);
                 int lb = (bx * S.nb + by) * S.nb + bz;
+                const int ch = item_size(a, v[i].x);
                 for (int c = 0; c < v[i].y; c++) {
                     Item it;
                     it.scene = sc;
                     it.block = lb;
-                    it.start = run.x + c * a.CH;
-                    it.count = min(a.CH, v[i].x - c * a.CH);
+                    it.start = run.x + c * ch;
+                    it.count = min(ch, v[i].x - c * ch);
                     a.L.items[run.y + c] = it;
                 }
                 if (v[i].z) a.L.gitems[run.z] = make_int2(sc, lb);

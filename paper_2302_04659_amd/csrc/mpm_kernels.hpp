@@ -59,6 +59,7 @@ struct SortArgs {
     Lists L;
     int B;
     int CH;                   // max particles per item
+    int cut;                  // the same for blocks that may be cut finer (item_size)
 };
 
 hipError_t launch_sort(const SortArgs &a, hipStream_t st);

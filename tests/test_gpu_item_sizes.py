@@ -45,3 +45,26 @@ def test_item_sizes(mpm, orc, n, block, fuse):
     assert rel_l2(gp, op, momentum_floor(sc, om.sum())) <= 1e-5
     sim.close()
     sim2.close()
+
+
+def test_dense_blocks_keep_their_items(mpm):
+    """40 particles to a cell in a small context: the blocks are not cut, so the
+    launch configuration with the same chunk gives the same sums, bit for bit
+    (one item per block: no order of float additions enters between blocks that
+    share no node)."""
+    rng = np.random.default_rng(3)
+    n = 2 * 2560
+    lo = np.repeat([4.5, 16.5], n // 2)[:, None] + rng.uniform(0.01, 3.99, size=(n, 3))
+    sc = scenes.small_scene(92, n=n, res=32, model=scenes.FLUID, colliders=False, dt=1e-4)
+    sc.x = (lo * sc.dx).astype(np.float32)
+    sc.v = rng.normal(size=(n, 3)).astype(np.float32)
+    grids = []
+    for copies in (1, 230):                # 5,120 particles, and enough scenes for chunks of 8,192 uncut
+        announce("dense blocks, scenes", copies)
+        sim = mpm.Sim([sc] + [scenes.small_scene(93, n=9200, res=32, model=scenes.FLUID, colliders=False)] * (copies - 1))
+        sim.set_option(mpm.OPT_CHUNK, 8192)
+        sim.set_option(mpm.OPT_CAPTURE_GRID, 1)
+        sim.step(1)
+        grids.append(sim.get_grid(0))
+        sim.close()
+    assert np.array_equal(grids[0][0], grids[1][0]) and np.array_equal(grids[0][1], grids[1][1])
