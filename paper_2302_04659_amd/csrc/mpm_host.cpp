@@ -575,6 +575,32 @@ mpm_status from_device(mpm_ctx ctx, void *dst, const void *src, size_t bytes, in
     return MPM_OK;
 }
 
+// Whether the boundary kernels can take the caller's device arrays themselves,
+// without a copy in d_io: memory of this device, no two of them overlapping and
+// none in the particle arrays (a copy in between is what gave such calls a
+// defined order).
+bool direct_io(mpm_ctx ctx, const std::pair<const float *, long long> (&arrays)[4])
+{
+    std::pair<uintptr_t, uintptr_t> used[8];
+    int nu = 0;
+    for (const float *P : ctx->d_P)
+        used[nu++] = {(uintptr_t)P, (uintptr_t)(P + (long long)NCOMP * ctx->pstride)};
+    for (const auto &a : arrays) {
+        if (!a.first) continue;
+        hipPointerAttribute_t at{};
+        if (hipPointerGetAttributes(&at, a.first) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        if (at.type != hipMemoryTypeDevice || at.device != ctx->dev || (uintptr_t)a.first % sizeof(float)) return false;
+        const uintptr_t lo = (uintptr_t)a.first, hi = lo + sizeof(float) * a.second;
+        for (int i = 0; i < nu; i++)
+            if (lo < used[i].second && used[i].first < hi) return false;
+        used[nu++] = {lo, hi};
+    }
+    return true;
+}
+
 void scene_range(mpm_ctx ctx, int scene, int &b, int &e)
 {
     if (scene < 0) {
@@ -935,6 +961,10 @@ mpm_status mpm_get_state(mpm_ctx ctx, int scene, float *x, float *v, float *C, f
     int b, e;
     scene_range(ctx, scene, b, e);
     long long n = e - b;
+    if (on_device && direct_io(ctx, {{x, 3 * n}, {v, 3 * n}, {C, 9 * n}, {F, 9 * n}})) {
+        HIPCHK(launch_get_state(ctx->d_scenes, ctx->d_psc, ctx->d_P[ctx->cur], ctx->pstride, b, e, x, v, C, F, ctx->stream));
+        return MPM_OK;
+    }
     float *dx_ = ctx->d_io, *dv_ = dx_ + 3 * n, *dC_ = dv_ + 3 * n, *dF_ = dC_ + 9 * n;
     HIPCHK(launch_get_state(ctx->d_scenes, ctx->d_psc, ctx->d_P[ctx->cur], ctx->pstride, b, e, x ? dx_ : nullptr,
                             v ? dv_ : nullptr, C ? dC_ : nullptr, F ? dF_ : nullptr, ctx->stream));
@@ -981,13 +1011,16 @@ mpm_status mpm_set_state(mpm_ctx ctx, int scene, const float *x, const float *v,
     if (!on_device) {
         for (long long k = 0; k < 3 * n; k++) ARGCHK(std::isfinite(x[k]) && std::isfinite(v[k]), "non-finite x / v");
     }
-    mpm_status st;
-    if ((st = to_device(ctx, dx_, x, 12 * n, on_device)) != MPM_OK) return st;
-    if ((st = to_device(ctx, dv_, v, 12 * n, on_device)) != MPM_OK) return st;
-    if ((st = to_device(ctx, dC_, C, 36 * n, on_device)) != MPM_OK) return st;
-    if ((st = to_device(ctx, dF_, F, 36 * n, on_device)) != MPM_OK) return st;
-    HIPCHK(launch_init_particles(ctx->d_scenes, ctx->n_scenes, ctx->d_psc, ctx->d_P[ctx->cur], ctx->pstride, dx_, dv_,
-                                 dC_, dF_, b, e, ctx->d_flags, ctx->stream));
+    if (!(on_device && direct_io(ctx, {{x, 3 * n}, {v, 3 * n}, {C, 9 * n}, {F, 9 * n}}))) {
+        mpm_status st;
+        if ((st = to_device(ctx, dx_, x, 12 * n, on_device)) != MPM_OK) return st;
+        if ((st = to_device(ctx, dv_, v, 12 * n, on_device)) != MPM_OK) return st;
+        if ((st = to_device(ctx, dC_, C, 36 * n, on_device)) != MPM_OK) return st;
+        if ((st = to_device(ctx, dF_, F, 36 * n, on_device)) != MPM_OK) return st;
+        x = dx_, v = dv_, C = dC_, F = dF_;
+    }
+    HIPCHK(launch_init_particles(ctx->d_scenes, ctx->n_scenes, ctx->d_psc, ctx->d_P[ctx->cur], ctx->pstride, x, v, C, F, b,
+                                 e, ctx->d_flags, ctx->stream));
     ctx->since_sort = 1 << 30;
     return MPM_OK;
 }
