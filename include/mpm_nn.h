@@ -44,6 +44,12 @@ extern "C" {
  * order uses 224 * ceil16(cout) of them). */
 int mpm_nn_pack(const float *w, int kind, int cin, int cout, int transpose, uint16_t *out, void *stream);
 
+/* mpm_nn_pack of `count` tensors, few launches for all of them; the arrays are
+ * host memory, read before the call returns.  w_cin[i] >= cin[i] are the input
+ * channels of w[i]'s rows, of which the first cin[i] are packed. */
+int mpm_nn_pack_many(int count, const float *const *w, const int *kind, const int *w_cin, const int *cin,
+                     const int *cout, const int *transpose, uint16_t *const *out, void *stream);
+
 /* y = act(conv(x) + bias): input [n][id][ih][iw] slice (cx, x_off, cin),
  * output slice (cy, y_off, cout); relu = 1 applies max(0, .); y32 (nullable)
  * additionally receives FP32 outputs [voxel][cy32]. */
@@ -111,6 +117,11 @@ int mpm_nn_masked_mse(const float *pred, int cp, const float *target, const floa
 /* One bias-corrected Adam step (t >= 1) on n FP32 parameters. */
 int mpm_nn_adam(float *p, const float *g, float *m, float *v, long long n, float lr, float beta1, float beta2,
                 float eps, int t, void *stream);
+
+/* The same step on `count` tensors, few launches for all of them; the arrays
+ * are host memory, read before the call returns. */
+int mpm_nn_adam_many(int count, float *const *p, const float *const *g, float *const *m, float *const *v,
+                     const long long *n, float lr, float beta1, float beta2, float eps, int t, void *stream);
 
 /* Crops of dense per-scene grids [n][R][R][R][c] (the surrogate runs on a
  * box around the material instead of the whole grid).

@@ -9,6 +9,7 @@
 namespace {
 
 int taps_of(int kind) { return kind == 0 || kind == 1 ? 27 : (kind == 2 ? 8 : 1); }
+constexpr int JOBS_AT_ONCE = 48;   // tensors of one pack or Adam launch
 int ceil16(int c) { return (c + 15) / 16 * 16; }
 int st_of(hipError_t e) { return e == hipSuccess ? 0 : -2; }
 bool kind_ok(int k) { return k >= 0 && k <= 3; }
@@ -80,10 +81,27 @@ extern "C" {
 
 int mpm_nn_pack(const float *w, int kind, int cin, int cout, int transpose, uint16_t *out, void *stream)
 {
-    if (!w || !out || !kind_ok(kind) || cin <= 0 || cout <= 0) return -1;
-    const int ci_e = transpose ? cout : cin, co_e = transpose ? cin : cout;
-    return st_of(nn::pack(w, taps_of(kind), cin, cout, ceil16(ci_e), ceil16(co_e), transpose, out,
-                          (hipStream_t)stream));
+    return mpm_nn_pack_many(1, &w, &kind, &cin, &cin, &cout, &transpose, &out, stream);
+}
+
+int mpm_nn_pack_many(int count, const float *const *w, const int *kind, const int *w_cin, const int *cin, const int *cout,
+                     const int *transpose, uint16_t *const *out, void *stream)
+{
+    if (count <= 0 || !w || !kind || !w_cin || !cin || !cout || !transpose || !out) return -1;
+    for (int i = 0; i < count; i++)
+        if (!w[i] || !out[i] || !kind_ok(kind[i]) || cin[i] <= 0 || cout[i] <= 0 || w_cin[i] < cin[i]) return -1;
+    nn::PackJob jobs[JOBS_AT_ONCE];
+    for (int i = 0; i < count; i += JOBS_AT_ONCE) {
+        const int n = count - i < JOBS_AT_ONCE ? count - i : JOBS_AT_ONCE;
+        for (int j = 0; j < n; j++) {
+            const int k = i + j, ci_e = transpose[k] ? cout[k] : cin[k], co_e = transpose[k] ? cin[k] : cout[k];
+            jobs[j] = nn::pack_job(w[k], taps_of(kind[k]), w_cin[k], cin[k], cout[k], ceil16(ci_e), ceil16(co_e),
+                                   transpose[k], out[k]);
+        }
+        const int r = st_of(nn::pack(jobs, n, (hipStream_t)stream));
+        if (r != 0) return r;
+    }
+    return 0;
 }
 
 int mpm_nn_conv(int kind, const uint16_t *x, int n, int id, int ih, int iw, int cx, int x_off, int cin,
@@ -177,8 +195,27 @@ int mpm_nn_masked_mse(const float *pred, int cp, const float *target, const floa
 int mpm_nn_adam(float *p, const float *g, float *m, float *v, long long n, float lr, float beta1, float beta2,
                 float eps, int t, void *stream)
 {
-    if (!p || !g || !m || !v || n <= 0 || t < 1) return -1;
-    return st_of(nn::adam(p, g, m, v, n, lr, beta1, beta2, eps, t, (hipStream_t)stream));
+    return mpm_nn_adam_many(1, &p, &g, &m, &v, &n, lr, beta1, beta2, eps, t, stream);
+}
+
+int mpm_nn_adam_many(int count, float *const *p, const float *const *g, float *const *m, float *const *v,
+                     const long long *n, float lr, float beta1, float beta2, float eps, int t, void *stream)
+{
+    if (count <= 0 || !p || !g || !m || !v || !n || t < 1) return -1;
+    for (int i = 0; i < count; i++)
+        if (!p[i] || !g[i] || !m[i] || !v[i] || n[i] <= 0) return -1;
+    nn::AdamJob jobs[JOBS_AT_ONCE];
+    for (int i = 0; i < count; i += JOBS_AT_ONCE) {
+        const int c = count - i < JOBS_AT_ONCE ? count - i : JOBS_AT_ONCE;
+        for (int j = 0; j < c; j++) {
+            const int k = i + j;
+            const uintptr_t bits = (uintptr_t)p[k] | (uintptr_t)g[k] | (uintptr_t)m[k] | (uintptr_t)v[k];
+            jobs[j] = {p[k], g[k], m[k], v[k], n[k], (bits & 15) == 0};
+        }
+        const int r = st_of(nn::adam(jobs, c, lr, beta1, beta2, eps, t, (hipStream_t)stream));
+        if (r != 0) return r;
+    }
+    return 0;
 }
 
 int mpm_nn_bbox(const float *field, int cf, int n, int R, int *bbox, void *stream)

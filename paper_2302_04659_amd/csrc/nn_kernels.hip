@@ -539,53 +539,57 @@ __global__ __launch_bounds__(256) void k_conv_first(ConvArgs a, ConvPlan p)
 //   k32 = 2: the first-layer order (8 input channels, taps folded into K):
 //            element ((c * NF + n) * 64 + lane) * 8 + j holds tap 4 c + lane / 16
 //            (zero for tap 27), channel j.
-__global__ void k_pack(const float *w, int ntap, int cin, int cout, int cin_p, int cout_p, int transpose, int k32,
-                       uint16_t *out)
+// The job of this workgroup: one comparison per lane.
+template <class Job>
+__device__ __forceinline__ int job_of(const Jobs<Job> &q)
 {
-    const int KC = cin_p / 16, NF = cout_p / 16;
-    const long long total = k32 == 2 ? (long long)FIRST_STEPS * NF * 512 : (long long)ntap * KC * NF * 256;
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total; e += (long long)gridDim.x * blockDim.x) {
-        int k, lane, n, t;
-        if (k32 == 2) {
-            const int j = (int)(e & 7);
-            lane = (int)((e >> 3) & 63);
-            const long long q = e >> 9;
-            n = (int)(q % NF);
-            t = 4 * (int)(q / NF) + (lane >> 4);
-            const int co = 16 * n + (lane & 15);
-            out[e] = f2bf(t < 27 && j < cin && co < cout ? w[((long long)t * cin + j) * cout + co] : 0.0f);
-            continue;
+    const int l = threadIdx.x & 63;
+    return __popcll(__ballot(l < q.count && (int)blockIdx.x >= q.first[l])) - 1;
+}
+
+// Threads take four elements in a row (one lane's fragment, or half of it) of
+// 1,024 per workgroup.  All the tensors of a network go into one launch: a
+// parameter update is bound by its launches, not by its 60 MB (see k_adam).
+__global__ __launch_bounds__(256) void k_pack(Jobs<PackJob> q)
+{
+    const int jn = job_of(q);
+    const PackJob a = q.j[jn];
+    const int KC = a.cin_p / 16, NF = a.cout_p / 16;
+    const long long e = ((long long)((int)blockIdx.x - q.first[jn]) * 256 + threadIdx.x) * 4;
+    if (e >= a.total) return;
+    float val[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (a.k32 == 2) {
+        const int lane = (int)((e >> 3) & 63);
+        const long long u = e >> 9;
+        const int n = (int)(u % NF), t = 4 * (int)(u / NF) + (lane >> 4), co = 16 * n + (lane & 15);
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int j = (int)(e & 7) + r;
+            if (t < 27 && j < a.cin && co < a.cout) val[r] = a.w[((long long)t * a.w_cin + j) * a.cout + co];
         }
-        if (!k32) {
-            const int r = (int)(e & 3);
-            lane = (int)((e >> 2) & 63);
-            long long q = e >> 8;
-            n = (int)(q % NF);
-            q /= NF;
-            const int c = (int)(q % KC);
-            t = (int)(q / KC);
-            k = 16 * c + 4 * (lane >> 4) + r;             // input channel of this conv
-        } else {
-            const int el = (int)(e & 7);
-            lane = (int)((e >> 3) & 63);
-            long long q = e >> 9;
-            n = (int)(q % NF);
-            q /= NF;
-            const int c = (int)(q % (KC / 2));
-            t = (int)(q / (KC / 2));
-            k = 32 * c + 8 * (lane >> 4) + el;
-        }
+    } else {
+        const int sh = a.k32 ? 9 : 8;
+        const int lane = (int)((e >> (sh - 6)) & 63), kc = a.k32 ? KC / 2 : KC;
+        long long u = e >> sh;
+        const int n = (int)(u % NF);
+        u /= NF;
+        const int c = (int)(u % kc), t = (int)(u / kc);
+        const int k0 = a.k32 ? 32 * c + 8 * (lane >> 4) + (int)(e & 7) : 16 * c + 4 * (lane >> 4);   // input channels of this conv
         const int j = 16 * n + (lane & 15);              // output channel of this conv
-        float v = 0.0f;
-        if (!transpose) {
-            if (k < cin && j < cout) v = w[((long long)t * cin + k) * cout + j];
-        } else {
-            // adjoint: this conv maps cout-channel gradients to cin-channel ones
-            const int tm = ntap - 1 - t;
-            if (k < cout && j < cin) v = w[((long long)tm * cin + j) * cout + k];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int k = k0 + r;
+            if (!a.transpose) {
+                if (k < a.cin && j < a.cout) val[r] = a.w[((long long)t * a.w_cin + k) * a.cout + j];
+            } else {
+                // adjoint: this conv maps cout-channel gradients to cin-channel ones
+                const int tm = a.ntap - 1 - t;
+                if (k < a.cout && j < a.cin) val[r] = a.w[((long long)tm * a.w_cin + j) * a.cout + k];
+            }
         }
-        out[e] = f2bf(v);
     }
+#pragma unroll
+    for (int r = 0; r < 4; r++) a.out[e + r] = f2bf(val[r]);
 }
 
 // ---------------------------------------------------------------- weight gradient
@@ -1181,17 +1185,39 @@ __global__ void k_masked_mse(const float *pred, int cp, const float *target, con
 }
 
 // Adam on FP32 master parameters (bias-corrected with step t)
-__global__ void k_adam(float *p, const float *g, float *m, float *v, long long n, float lr, float b1, float b2, float eps,
-                       int t)
+// 1,024 elements per workgroup, 28 bytes each; every parameter tensor of the
+// network in one launch (34 launches of a few microseconds each, with as many
+// for the weight fragments, were ADAM_BEFORE us an update; two are ADAM_AFTER).
+__global__ __launch_bounds__(256) void k_adam(Jobs<AdamJob> q, float lr, float b1, float b2, float eps, int t)
 {
+    const int jn = job_of(q);
+    const AdamJob a = q.j[jn];
     const float c1 = 1.0f / (1.0f - powf(b1, (float)t)), c2 = 1.0f / (1.0f - powf(b2, (float)t));
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
-        float gg = g[e];
-        float mm = b1 * m[e] + (1.0f - b1) * gg;
-        float vv = b2 * v[e] + (1.0f - b2) * gg * gg;
-        m[e] = mm;
-        v[e] = vv;
-        p[e] -= lr * (mm * c1) / (sqrtf(vv * c2) + eps);
+    const long long base = (long long)((int)blockIdx.x - q.first[jn]) * 1024;
+    auto update = [&](float &p, float g, float &m, float &v) {
+        m = b1 * m + (1.0f - b1) * g;
+        v = b2 * v + (1.0f - b2) * g * g;
+        p -= lr * (m * c1) / (sqrtf(v * c2) + eps);
+    };
+    if (a.vec && base + 1024 <= a.n) {
+        const long long e = base / 4 + threadIdx.x;
+        const float4 g = ((const float4 *)a.g)[e];
+        float4 p = ((float4 *)a.p)[e], m = ((float4 *)a.m)[e], v = ((float4 *)a.v)[e];
+        update(p.x, g.x, m.x, v.x);
+        update(p.y, g.y, m.y, v.y);
+        update(p.z, g.z, m.z, v.z);
+        update(p.w, g.w, m.w, v.w);
+        ((float4 *)a.m)[e] = m;
+        ((float4 *)a.v)[e] = v;
+        ((float4 *)a.p)[e] = p;
+        return;
+    }
+    for (long long e = base + threadIdx.x; e < a.n && e < base + 1024; e += 256) {
+        float p = a.p[e], m = a.m[e], v = a.v[e];
+        update(p, a.g[e], m, v);
+        a.m[e] = m;
+        a.v[e] = v;
+        a.p[e] = p;
     }
 }
 
@@ -1465,20 +1491,39 @@ hipError_t conv(const ConvArgs &a, hipStream_t st)
     return nf >= 4 && (nvox + 15) / 16 * (nf / 4) >= 2048 ? conv_direct<4>(a, st) : conv_direct<2>(a, st);
 }
 
-hipError_t pack(const float *w, int ntap, int cin, int cout, int cin_p, int cout_p, int transpose, uint16_t *out,
-                hipStream_t st)
+PackJob pack_job(const float *w, int ntap, int w_cin, int cin, int cout, int cin_p, int cout_p, int transpose, uint16_t *out)
 {
-    const long long total = (long long)ntap * (cin_p / 16) * (cout_p / 16) * 256;
     // 3^3 kernels with a multiple of 32 input channels run on 16x16x32 fragments, and so does the
     // 3^3 layer over 8 input channels (taps folded into K)
     const int k32 = ntap == 27 && !transpose && cin == 8 ? 2 : (ntap == 27 && cin_p % 32 == 0);
-    if (k32 == 2) {
-        const long long n2 = (long long)FIRST_STEPS * (cout_p / 16) * 512;
-        k_pack<<<grid_for(n2), 256, 0, st>>>(w, ntap, cin, cout, cin_p, cout_p, transpose, k32, out);
-        return hipGetLastError();
+    const long long total = k32 == 2 ? (long long)FIRST_STEPS * (cout_p / 16) * 512
+                                     : (long long)ntap * (cin_p / 16) * (cout_p / 16) * 256;
+    return {w, out, total, ntap, w_cin, cin, cout, cin_p, cout_p, transpose, k32};
+}
+
+// Launches `count` jobs, Jobs::MAX at a time; size(job): its workgroups.
+template <class Job, class Size, class Launch>
+static hipError_t launch_jobs(const Job *jobs, int count, Size size, Launch launch)
+{
+    for (int i = 0; i < count; i += Jobs<Job>::MAX) {
+        Jobs<Job> q;
+        q.count = std::min(count - i, Jobs<Job>::MAX);
+        q.first[0] = 0;
+        for (int j = 0; j < q.count; j++) {
+            q.j[j] = jobs[i + j];
+            q.first[j + 1] = q.first[j] + size(jobs[i + j]);
+        }
+        launch(q, (unsigned)q.first[q.count]);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    k_pack<<<grid_for(total), 256, 0, st>>>(w, ntap, cin, cout, cin_p, cout_p, transpose, k32, out);
-    return hipGetLastError();
+    return hipSuccess;
+}
+
+hipError_t pack(const PackJob *jobs, int count, hipStream_t st)
+{
+    return launch_jobs(jobs, count, [](const PackJob &j) { return (int)((j.total + 1023) / 1024); },
+                       [&](const Jobs<PackJob> &q, unsigned g) { k_pack<<<g, 256, 0, st>>>(q); });
 }
 
 // Tile and wave split of a weight gradient: the tile shape (z, x positions)
@@ -1681,11 +1726,10 @@ hipError_t crop(const float *src, int c, int n, int R, const int *origin, int D,
     return hipGetLastError();
 }
 
-hipError_t adam(float *p, const float *g, float *m, float *v, long long n, float lr, float b1, float b2, float eps, int t,
-                hipStream_t st)
+hipError_t adam(const AdamJob *jobs, int count, float lr, float b1, float b2, float eps, int t, hipStream_t st)
 {
-    k_adam<<<grid_for(n), 256, 0, st>>>(p, g, m, v, n, lr, b1, b2, eps, t);
-    return hipGetLastError();
+    return launch_jobs(jobs, count, [](const AdamJob &j) { return (int)((j.n + 1023) / 1024); },
+                       [&](const Jobs<AdamJob> &q, unsigned g) { k_adam<<<g, 256, 0, st>>>(q, lr, b1, b2, eps, t); });
 }
 
 }  // namespace nn

@@ -36,8 +36,31 @@ struct WgradArgs {
 };
 
 hipError_t conv(const ConvArgs &a, hipStream_t st);
-hipError_t pack(const float *w, int ntap, int cin, int cout, int cin_p, int cout_p, int transpose, uint16_t *out,
-                hipStream_t st);
+// One tensor's weights to pack, as k_pack's comment has it.
+struct PackJob {
+    const float *w;
+    uint16_t *out;
+    long long total;          // elements of out
+    int ntap, w_cin;          // w_cin: input channels of w's rows, of which the first cin are packed
+    int cin, cout, cin_p, cout_p, transpose, k32;
+};
+struct AdamJob {
+    float *p;
+    const float *g;
+    float *m, *v;
+    long long n;
+    int vec;                  // all four on 16-byte boundaries
+};
+// The tensors of one launch, by value: job j takes the workgroups first[j] .. first[j + 1].
+template <class Job>
+struct Jobs {
+    static constexpr int MAX = 48;
+    int count;
+    int first[MAX + 1];
+    Job j[MAX];
+};
+PackJob pack_job(const float *w, int ntap, int w_cin, int cin, int cout, int cin_p, int cout_p, int transpose, uint16_t *out);
+hipError_t pack(const PackJob *jobs, int count, hipStream_t st);
 hipError_t wgrad(const WgradArgs &a, hipStream_t st);
 hipError_t bias_grad(const uint16_t *g, long long nvox, int cg, int g_off, int cout, float *gb, int accumulate,
                      hipStream_t st);
@@ -55,7 +78,6 @@ hipError_t bbox(const float *field, int cf, int n, int R, int *box, hipStream_t 
 hipError_t crop_origin(const int *box, int n, int R, int D, int H, int W, int *origin, hipStream_t st);
 hipError_t crop(const float *src, int c, int n, int R, const int *origin, int D, int H, int W, float *dst, int uncrop,
                 hipStream_t st);
-hipError_t adam(float *p, const float *g, float *m, float *v, long long n, float lr, float b1, float b2, float eps, int t,
-                hipStream_t st);
+hipError_t adam(const AdamJob *jobs, int count, float lr, float b1, float b2, float eps, int t, hipStream_t st);
 
 }  // namespace nn

@@ -62,6 +62,7 @@ def nn_lib():
     if not getattr(L, "_nn_ready", False):
         vp, i, ll, f = ct.c_void_p, ct.c_int, ct.c_longlong, ct.c_float
         L.mpm_nn_pack.argtypes = [vp, i, i, i, i, vp, vp]
+        L.mpm_nn_pack_many.argtypes = [i, vp, vp, vp, vp, vp, vp, vp, vp]
         L.mpm_nn_conv.argtypes = [i, vp, i, i, i, i, i, i, i, vp, vp, i, vp, i, i, i, vp, i, vp]
         L.mpm_nn_wgrad.argtypes = [i, vp, i, i, i, i, i, i, i, vp, i, i, i, ll, vp, vp, i, vp]
         L.mpm_nn_bias_grad.argtypes = [vp, ll, i, i, i, vp, i, vp]
@@ -71,6 +72,7 @@ def nn_lib():
         L.mpm_nn_to_bf16.argtypes = [vp, i, ll, i, vp, i, i, i, vp]
         L.mpm_nn_masked_mse.argtypes = [vp, i, vp, vp, ll, i, vp, i, vp, i, vp]
         L.mpm_nn_adam.argtypes = [vp, vp, vp, vp, ll, f, f, f, f, i, vp]
+        L.mpm_nn_adam_many.argtypes = [i, vp, vp, vp, vp, vp, f, f, f, f, i, vp]
         L.mpm_nn_bbox.argtypes = [vp, i, i, i, vp, vp]
         L.mpm_nn_crop_origin.argtypes = [vp, i, i, i, i, i, vp, vp]
         L.mpm_nn_crop.argtypes = [vp, i, i, i, vp, i, i, i, vp, i, vp]
@@ -139,20 +141,26 @@ class UNet:
 
     # ------------------------------------------------------------------ weights
     def repack(self):
+        """New BF16 fragments of every layer (forward and adjoint) in one buffer."""
         torch = self.torch
-        for name, kind, ci, co, _ in self.layers:
-            w = self.params[name + ".w"]
-            taps = TAPS[kind]
-            fw = torch.zeros(taps * _ceil16(ci) * _ceil16(co), dtype=torch.int16, device=self.device)
-            if name == "e1a" and self.cin == 8:
-                # the first layer sees the 8 real input channels (taps folded into the MFMA K)
-                w8 = w[:, :8, :].contiguous()
-                _chk(self.L.mpm_nn_pack(w8.data_ptr(), KIND[kind], 8, co, 0, fw.data_ptr(), self.stream), "pack")
-            else:
-                _chk(self.L.mpm_nn_pack(w.data_ptr(), KIND[kind], ci, co, 0, fw.data_ptr(), self.stream), "pack")
-            bw = torch.zeros(taps * _ceil16(co) * _ceil16(ci), dtype=torch.int16, device=self.device)
-            _chk(self.L.mpm_nn_pack(w.data_ptr(), KIND[kind], ci, co, 1, bw.data_ptr(), self.stream), "pack")
-            self.packs[name] = (fw, bw)
+        kind, w_cin, cin, cout, tr, sizes = [], [], [], [], [], []
+        for name, k, ci, co, _ in self.layers:
+            # the first layer sees the 8 real input channels (taps folded into the MFMA K)
+            for t, c in ((0, 8 if name == "e1a" and self.cin == 8 else ci), (1, ci)):
+                kind.append(KIND[k])
+                w_cin.append(ci)
+                cin.append(c)
+                cout.append(co)
+                tr.append(t)
+                sizes.append(TAPS[k] * _ceil16(ci) * _ceil16(co))
+        n = len(kind)
+        out = torch.empty(sum(sizes), dtype=torch.int16, device=self.device).split(sizes)
+        w = [self.params[layer[0] + ".w"].data_ptr() for layer in self.layers for _ in (0, 1)]
+        ints, ptrs = ct.c_int * n, ct.c_void_p * n
+        _chk(self.L.mpm_nn_pack_many(n, ptrs(*w), ints(*kind), ints(*w_cin), ints(*cin), ints(*cout), ints(*tr),
+                                     ptrs(*[o.data_ptr() for o in out]), self.stream), "pack")
+        for i, layer in enumerate(self.layers):
+            self.packs[layer[0]] = (out[2 * i], out[2 * i + 1])
 
     def export_weights(self) -> bytes:
         """The weight blob of mpm_surrogate_load (include/mpm.h): an int32
@@ -363,10 +371,12 @@ class UNet:
 
     def adam(self, lr=3e-4, b1=0.9, b2=0.999, eps=1e-8):
         self.step_t += 1
-        for k, p in self.params.items():
-            _chk(self.L.mpm_nn_adam(p.data_ptr(), self.grads[k].data_ptr(), self.adam_m[k].data_ptr(),
-                                    self.adam_v[k].data_ptr(), p.numel(), lr, b1, b2, eps, self.step_t, self.stream),
-                 "adam")
+        keys, n = list(self.params), len(self.params)
+        ptrs = ct.c_void_p * n
+        groups = (self.params, self.grads, self.adam_m, self.adam_v)
+        _chk(self.L.mpm_nn_adam_many(n, *[ptrs(*[g[k].data_ptr() for k in keys]) for g in groups],
+                                     (ct.c_longlong * n)(*[self.params[k].numel() for k in keys]), lr, b1, b2, eps,
+                                     self.step_t, self.stream), "adam")
         self.repack()
 
     def train_step(self, x, target, mask, lr=3e-4):
