@@ -1187,7 +1187,7 @@ __global__ void k_masked_mse(const float *pred, int cp, const float *target, con
 // Adam on FP32 master parameters (bias-corrected with step t)
 // 1,024 elements per workgroup, 28 bytes each; every parameter tensor of the
 // network in one launch (34 launches of a few microseconds each, with as many
-// for the weight fragments, were ADAM_BEFORE us an update; two are ADAM_AFTER).
+// for the weight fragments, were 553 us an update; two are 61).
 __global__ __launch_bounds__(256) void k_adam(Jobs<AdamJob> q, float lr, float b1, float b2, float eps, int t)
 {
     const int jn = job_of(q);
