@@ -368,6 +368,9 @@ SortArgs sort_args(mpm_ctx ctx)
     a.n_scenes = ctx->n_scenes;
     a.psc = ctx->d_psc;
     a.P = ctx->d_P[ctx->cur];
+    a.x = a.P + (long long)X0 * ctx->pstride;
+    a.x_comp = ctx->pstride;
+    a.x_part = 1;
     a.Pn = ctx->d_P[1 - ctx->cur];
     a.pstride = ctx->pstride;
     a.N = ctx->N;
@@ -423,10 +426,17 @@ StepArgs step_args(mpm_ctx ctx, int substep)
     return a;
 }
 
-mpm_status do_sort(mpm_ctx ctx)
+// rows: the whole state comes from there, sorted as it is read.
+mpm_status do_sort(mpm_ctx ctx, const StateRows *rows = nullptr)
 {
     KTimer kt(ctx, MPM_K_SORT);
-    HIPCHK(launch_sort(sort_args(ctx), ctx->stream));
+    SortArgs a = sort_args(ctx);
+    if (rows) {
+        a.x = rows->x;
+        a.x_comp = 1;
+        a.x_part = 3;
+    }
+    HIPCHK(launch_sort(a, rows, ctx->d_flags, ctx->stream));
     ctx->cnt[MPM_CNT_SORTS]++;
     ctx->cur = 1 - ctx->cur;
     ctx->since_sort = 0;
@@ -1018,6 +1028,10 @@ mpm_status mpm_set_state(mpm_ctx ctx, int scene, const float *x, const float *v,
         if ((st = to_device(ctx, dC_, C, 36 * n, on_device)) != MPM_OK) return st;
         if ((st = to_device(ctx, dF_, F, 36 * n, on_device)) != MPM_OK) return st;
         x = dx_, v = dv_, C = dC_, F = dF_;
+    }
+    if (n == ctx->N && n > 0) {
+        const StateRows rows = {x, v, C, F};
+        return do_sort(ctx, &rows);
     }
     HIPCHK(launch_init_particles(ctx->d_scenes, ctx->n_scenes, ctx->d_psc, ctx->d_P[ctx->cur], ctx->pstride, x, v, C, F, b,
                                  e, ctx->d_flags, ctx->stream));

@@ -72,7 +72,7 @@ __device__ __forceinline__ unsigned particle_key(const SortArgs &a, int j)
     const SceneDev &S = a.scenes[s];
     int b[3], cl = 0;
     float f;
-    for (int d = 0; d < 3; d++) particle_base(S, a.P[(long long)(X0 + d) * a.pstride + j], b[d], f, cl);
+    for (int d = 0; d < 3; d++) particle_base(S, a.x[d * a.x_comp + j * a.x_part], b[d], f, cl);
     return (unsigned)a.scene_bin_off[s] + morton3(b[0] / a.B, b[1] / a.B, b[2] / a.B);
 }
 
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(WG) void k_bank_order(SortArgs a)
             float f;
             for (int d = 0; d < 3; d++) {
                 int b;
-                particle_base(S, a.P[(long long)(X0 + d) * a.pstride + j], b, f, cl);
+                particle_base(S, a.x[d * a.x_comp + j * a.x_part], b, f, cl);
                 tb[d] = min(max(b - org[d], 0), T - 1);
             }
             const int c = ((tb[0] * T + tb[1]) * T + tb[2]) % BANK_CLASSES;
@@ -477,7 +477,63 @@ __global__ __launch_bounds__(WG) void k_item_bounds(SortArgs a)
     }
 }
 
-hipError_t launch_sort(const SortArgs &a, hipStream_t st)
+// A non-finite x, v, C or F (or an F whose stress is not defined) sets the
+// scene's FLAG_NONFINITE: inside a substep the fixed-point P2G would turn it
+// into finite garbage rather than propagate it.
+__device__ __forceinline__ void init_particle(const SceneDev *scenes, int s, const float (&x)[3], const float (&v)[3],
+                                              const float (&C)[9], const float (&F)[9], float *P, long long ps, int slot,
+                                              int id, int *flags)
+{
+    const SceneDev &S = scenes[s];
+    const Material mat = material_of(S);
+    const float mass = S.mass, kstress = S.kstress;   // before the stores, which may alias the scene for the compiler
+    float G[9], tau[9];
+#pragma unroll
+    for (int e = 0; e < 9; e++) G[e] = F[e] - (e % 4 == 0 ? 1.0f : 0.0f);
+    int bad = 0;
+    stress_of(G, mat, tau, bad);
+    float chk = 0.0f;   // NaN or infinity in any input makes it fail the test below
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
+        chk += fabsf(x[d]) + fabsf(v[d]);
+        P[(X0 + d) * ps + slot] = x[d];
+        P[(V0 + d) * ps + slot] = v[d];
+    }
+#pragma unroll
+    for (int e = 0; e < 9; e++) chk += fabsf(G[e]) + fabsf(C[e]) + fabsf(tau[e]);
+    if (bad || !(chk <= 3.0e38f)) atomicOr(flags + s, (int)FLAG_NONFINITE);
+#pragma unroll
+    for (int e = 0; e < 9; e++) {
+        P[(A00 + e) * ps + slot] = fmaf(mass, C[e], -kstress * tau[e]);
+        P[(G00 + e) * ps + slot] = G[e];
+    }
+    P[PID * ps + slot] = __int_as_float(id);
+}
+
+template <int N>
+__device__ __forceinline__ void load_row(float (&r)[N], const float *src)
+{
+    __builtin_memcpy(r, src, sizeof(r));   // the widest loads that a 4-byte alignment allows
+}
+
+// k_gather for a state handed in as rows: each particle goes straight to its
+// sorted slot, its 24 floats in 5 or 6 cache lines where the gather from
+// component arrays in creation order takes 25 (7.7 million particles: in and
+// gather 460 + 995 -> 537 us).
+__global__ __launch_bounds__(WG) void k_gather_rows(SortArgs a, StateRows w, int *flags)
+{
+    const int p = xcd_remap(blockIdx.x, gridDim.x) * WG + threadIdx.x;
+    if (p >= a.N) return;
+    const long long j = a.perm2[p];
+    float x[3], v[3], C[9], F[9];
+    load_row(x, w.x + 3 * j);
+    load_row(v, w.v + 3 * j);
+    load_row(C, w.C + 9 * j);
+    load_row(F, w.F + 9 * j);
+    init_particle(a.scenes, a.psc[p], x, v, C, F, a.Pn, a.pstride, p, (int)j, flags);
+}
+
+hipError_t launch_sort(const SortArgs &a, const StateRows *rows, int *flags, hipStream_t st)
 {
     int gN = (a.N + WG - 1) / WG, gT = (a.T + WG - 1) / WG;
     int ntiles = (a.T + SCAN_TILE - 1) / SCAN_TILE;
@@ -499,7 +555,8 @@ hipError_t launch_sort(const SortArgs &a, hipStream_t st)
         else k_scatter<1><<<gS, WG, 0, st>>>(a);
         if (a.B == 4) k_bank_order<4><<<2048, WG, 0, st>>>(a);
         else k_bank_order<8><<<2048, WG, 0, st>>>(a);
-        k_gather<<<gN8, WG, 0, st>>>(a);
+        if (rows) k_gather_rows<<<gN8, WG, 0, st>>>(a, *rows, flags);
+        else k_gather<<<gN8, WG, 0, st>>>(a);
         k_item_bounds<<<2048, WG, 0, st>>>(a);
     }
     return hipGetLastError();
@@ -1710,9 +1767,6 @@ __device__ __forceinline__ void stage_rows(const float *src, float *lds, int n)
     for (int q = threadIdx.x; q < n; q += WG) lds[q] = src[q];
 }
 
-// A non-finite x, v, C or F (or an F whose stress is not defined) sets the
-// scene's FLAG_NONFINITE: inside a substep the fixed-point P2G would turn it
-// into finite garbage rather than propagate it.
 // Bound by memory (96 B in, 100 B out a particle).  The rows of 3 and 9 floats
 // go through LDS (odd strides: no bank conflicts), so that each load instruction
 // of a wave takes 256 bytes in a row instead of every 36th (7.7 million
@@ -1731,30 +1785,18 @@ __global__ __launch_bounds__(WG) void k_init_particles(const SceneDev *scenes, c
     __syncthreads();
     const int t = threadIdx.x, i = i0 + t;
     if (t >= n) return;
-    const SceneDev &S = scenes[psc[i]];
-    Material mat = material_of(S);
-    float G[9], Cm[9], tau[9];
-    for (int e = 0; e < 9; e++) {
-        G[e] = F ? lF[9 * t + e] - (e % 4 == 0 ? 1.0f : 0.0f) : 0.0f;
-        Cm[e] = C ? lC[9 * t + e] : 0.0f;
-    }
-    int bad = 0;
-    stress_of(G, mat, tau, bad);
-    float chk = 0.0f;   // NaN or infinity in any input makes it fail the test below
+    float xr[3], vr[3], Cr[9], Fr[9];
+#pragma unroll
     for (int d = 0; d < 3; d++) {
-        const float xv = lx[3 * t + d], vv = v ? lv[3 * t + d] : 0.0f;
-        chk += fabsf(xv) + fabsf(vv);
-        P[(X0 + d) * ps + i] = xv;
-        P[(V0 + d) * ps + i] = vv;
+        xr[d] = lx[3 * t + d];
+        vr[d] = v ? lv[3 * t + d] : 0.0f;
     }
-    for (int e = 0; e < 9; e++) chk += fabsf(G[e]) + fabsf(Cm[e]) + fabsf(tau[e]);
-    if (bad || !(chk <= 3.0e38f)) atomicOr(flags + psc[i], (int)FLAG_NONFINITE);
-    const float mass = S.mass, kstress = S.kstress;   // before the stores, which may alias the scene for the compiler
+#pragma unroll
     for (int e = 0; e < 9; e++) {
-        P[(A00 + e) * ps + i] = fmaf(mass, Cm[e], -kstress * tau[e]);
-        P[(G00 + e) * ps + i] = G[e];
+        Cr[e] = C ? lC[9 * t + e] : 0.0f;
+        Fr[e] = F ? lF[9 * t + e] : (e % 4 == 0 ? 1.0f : 0.0f);
     }
-    P[PID * ps + i] = __int_as_float(i);
+    init_particle(scenes, psc[i], xr, vr, Cr, Fr, P, ps, i, i, flags);
 }
 
 hipError_t launch_init_particles(const SceneDev *scenes, int n_scenes, const int *psc, float *P, long long pstride,

@@ -44,6 +44,8 @@ struct SortArgs {
     int n_scenes;
     const int *psc;           // scene of each particle slot
     const float *P;           // current buffer
+    const float *x;           // positions to sort by: component d of particle j at x[d * x_comp + j * x_part]
+    long long x_comp, x_part;
     float *Pn;                // other buffer
     long long pstride;
     int N;                    // particle slots in use
@@ -62,7 +64,12 @@ struct SortArgs {
     int cut;                  // the same for blocks that may be cut finer (item_size)
 };
 
-hipError_t launch_sort(const SortArgs &a, hipStream_t st);
+// A whole state handed in, rows in creation order.
+struct StateRows {
+    const float *x, *v, *C, *F;
+};
+// rows: the particles come from there (a.x too), not from a.P.
+hipError_t launch_sort(const SortArgs &a, const StateRows *rows, int *flags, hipStream_t st);
 // The next P2G / grid / G2P / G2P2G launch on this thread records start and
 // stop into these events at the kernel's own start and end.
 void time_next_launch(hipEvent_t start, hipEvent_t stop);
