@@ -135,10 +135,8 @@ __global__ __launch_bounds__(WG) void k_keys(SortArgs a)
 // block itself and its upper neighbours (a stencil spans base .. base + 2).
 // Mass a drifted particle puts one block lower is queued on the overflow
 // list by P2G itself.
-__global__ __launch_bounds__(WG) void k_dilate(SortArgs a)
+__device__ __forceinline__ int dilate_bin(const SortArgs &a, int b)
 {
-    int b = blockIdx.x * WG + threadIdx.x;
-    if (b >= a.T) return;
     int s = scene_of_bin(a.scene_bin_off, a.n_scenes, b);
     const SceneDev &S = a.scenes[s];
     int off = a.scene_bin_off[s];
@@ -152,8 +150,14 @@ __global__ __launch_bounds__(WG) void k_dilate(SortArgs a)
                 if (x < 0 || y < 0 || z < 0 || x >= nb || y >= nb || z >= nb) continue;
                 hit |= a.count[off + morton3(x, y, z)] > 0;
             }
-    a.dil[b] = (unsigned char)hit;
     a.L.bflag[off + (bx * nb + by) * nb + bz] = hit ? 2 : 0;
+    return hit;
+}
+
+__global__ __launch_bounds__(WG) void k_dilate(SortArgs a)
+{
+    int b = blockIdx.x * WG + threadIdx.x;
+    if (b < a.T) a.dil[b] = (unsigned char)dilate_bin(a, b);
 }
 
 static constexpr int SCAN_PER = 8;
@@ -171,19 +175,24 @@ __device__ __forceinline__ int item_size(const SortArgs &a, int c)
     return c <= 12 * a.B * a.B * a.B ? a.cut : a.CH;
 }
 
+__device__ __forceinline__ int3 bin_triple(const SortArgs &a, int b, int dil)
+{
+    const int c = a.count[b], ch = item_size(a, c);
+    return make_int3(c, (c + ch - 1) / ch, dil);
+}
+
 __device__ __forceinline__ int3 bin_triple(const SortArgs &a, int b)
 {
-    if (b >= a.T) return make_int3(0, 0, 0);
-    const int c = a.count[b], ch = item_size(a, c);
-    return make_int3(c, (c + ch - 1) / ch, (int)a.dil[b]);
+    return b < a.T ? bin_triple(a, b, (int)a.dil[b]) : make_int3(0, 0, 0);
 }
 
 __device__ __forceinline__ int3 add3(int3 x, int3 y) { return make_int3(x.x + y.x, x.y + y.y, x.z + y.z); }
 
 // Exclusive scan of one int3 per thread over the workgroup; returns the total.
+template <int NT = WG>
 __device__ int3 block_exscan3(int3 v, int3 &excl)
 {
-    __shared__ int3 wsum[WG / 64];
+    __shared__ int3 wsum[NT / 64];
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int3 inc = v;
     for (int o = 1; o < 64; o <<= 1) {
@@ -196,7 +205,7 @@ __device__ int3 block_exscan3(int3 v, int3 &excl)
     if (lane == 63) wsum[w] = inc;
     __syncthreads();
     int3 before = make_int3(0, 0, 0), total = make_int3(0, 0, 0);
-    for (int i = 0; i < WG / 64; i++) {
+    for (int i = 0; i < NT / 64; i++) {
         if (i < w) before = add3(before, wsum[i]);
         total = add3(total, wsum[i]);
     }
@@ -234,6 +243,34 @@ __global__ __launch_bounds__(WG) void k_scan_top(SortArgs a, int ntiles)
     }
 }
 
+// v: the bin's counts (bin_triple), run: their sums over the bins before it.
+__device__ void emit_bin(const SortArgs &a, int b, int3 v, int3 run)
+{
+    a.pstart[b] = run.x;
+    int sc = scene_of_bin(a.scene_bin_off, a.n_scenes, b);
+    int off = a.scene_bin_off[sc];
+    if (b == off) {
+        a.L.scene_item_begin[sc] = run.y;
+        a.L.scene_gitem_begin[sc] = run.z;
+    }
+    if (v.x > 0 || v.z > 0) {
+        const SceneDev &S = a.scenes[sc];
+        uint32_t m = (uint32_t)(b - off);
+        int bx = compact3(m), by = compact3(m >> 1), bz = compact3(m >> 2);
+        int lb = (bx * S.nb + by) * S.nb + bz;
+        const int ch = item_size(a, v.x);
+        for (int c = 0; c < v.y; c++) {
+            Item it;
+            it.scene = sc;
+            it.block = lb;
+            it.start = run.x + c * ch;
+            it.count = min(ch, v.x - c * ch);
+            a.L.items[run.y + c] = it;
+        }
+        if (v.z) a.L.gitems[run.z] = make_int2(sc, lb);
+    }
+}
+
 __global__ __launch_bounds__(WG) void k_scan_emit(SortArgs a)
 {
     int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_PER;
@@ -247,32 +284,7 @@ __global__ __launch_bounds__(WG) void k_scan_emit(SortArgs a)
     block_exscan3(s, ex);
     int3 run = add3(ex, a.tsum[blockIdx.x]);
     for (int i = 0; i < SCAN_PER; i++) {
-        int b = base + i;
-        if (b < a.T) {
-            a.pstart[b] = run.x;
-            int sc = scene_of_bin(a.scene_bin_off, a.n_scenes, b);
-            int off = a.scene_bin_off[sc];
-            if (b == off) {
-                a.L.scene_item_begin[sc] = run.y;
-                a.L.scene_gitem_begin[sc] = run.z;
-            }
-            if (v[i].x > 0 || v[i].z > 0) {
-                const SceneDev &S = a.scenes[sc];
-                uint32_t m = (uint32_t)(b - off);
-                int bx = compact3(m), by = compact3(m >> 1), bz = compact3(m >> 2);
-                int lb = (bx * S.nb + by) * S.nb + bz;
-                const int ch = item_size(a, v[i].x);
-                for (int c = 0; c < v[i].y; c++) {
-                    Item it;
-                    it.scene = sc;
-                    it.block = lb;
-                    it.start = run.x + c * ch;
-                    it.count = min(ch, v[i].x - c * ch);
-                    a.L.items[run.y + c] = it;
-                }
-                if (v[i].z) a.L.gitems[run.z] = make_int2(sc, lb);
-            }
-        }
+        if (base + i < a.T) emit_bin(a, base + i, v[i], run);
         run = add3(run, v[i]);
     }
 }
@@ -449,6 +461,65 @@ __global__ __launch_bounds__(1024) void k_item_order(SortArgs a)
         a.L.order[atomicAdd(&cnt[order_class(a.L.items[it].count, a.CH)], 1)] = it;
 }
 
+// k_dilate, the three scan kernels and k_item_order in one workgroup, for few
+// bins: five dependent launches of a few microseconds each were most of a small
+// context's sort (8,192 particles, 512 bins: 23.7 us and the gaps between them
+// -> 10.9 us).  Up to two bins a thread: at 4,096 bins the eight counts that each
+// reads for its neighbours wait on one CU, 21.5 us against about as much.
+constexpr int SMALL_PER = 2, SMALL_BINS = SMALL_PER * 1024;
+
+__global__ __launch_bounds__(1024) void k_plan_small(SortArgs a)
+{
+    __shared__ int cls[ORDER_CLASSES];
+    static_assert(ORDER_CLASSES == 64, "one class per lane");
+    const int t = threadIdx.x, per = (a.T + 1023) / 1024, base = t * per;
+    if (t < ORDER_CLASSES) cls[t] = 0;
+    int3 v[SMALL_PER], sum = make_int3(0, 0, 0), run;
+#pragma unroll
+    for (int i = 0; i < SMALL_PER; i++) {
+        v[i] = make_int3(0, 0, 0);
+        if (i < per && base + i < a.T) v[i] = bin_triple(a, base + i, dilate_bin(a, base + i));
+        sum = add3(sum, v[i]);
+    }
+    const int3 total = block_exscan3<1024>(sum, run);
+    if (t == 0) {
+        *a.L.n_items = total.y;
+        *a.L.n_gitems = total.z;
+        a.L.scene_item_begin[a.n_scenes] = total.y;
+        a.L.scene_gitem_begin[a.n_scenes] = total.z;
+    }
+    const int item0 = run.y;
+#pragma unroll
+    for (int i = 0; i < SMALL_PER; i++) {
+        if (i >= per || base + i >= a.T) break;
+        emit_bin(a, base + i, v[i], run);
+        run = add3(run, v[i]);
+    }
+    // the items' dispatch order, as k_item_order's: f(item, class) over this thread's items
+    auto own_items = [&](auto f) {
+        int it = item0;
+#pragma unroll
+        for (int i = 0; i < SMALL_PER; i++) {
+            const int ch = item_size(a, v[i].x);
+            for (int c = 0; c < v[i].y; c++, it++) f(it, order_class(min(ch, v[i].x - c * ch), a.CH));
+        }
+    };
+    own_items([&](int, int c) { atomicAdd(&cls[c], 1); });
+    __syncthreads();
+    if (t < ORDER_CLASSES) {
+        // classes from the largest down: lane t holds class 63 - t, its first slot is the sum before it
+        const int n = cls[ORDER_CLASSES - 1 - t];
+        int inc = n;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int u = __shfl_up(inc, o, 64);
+            if (t >= o) inc += u;
+        }
+        cls[ORDER_CLASSES - 1 - t] = inc - n;
+    }
+    __syncthreads();
+    own_items([&](int it, int c) { a.L.order[atomicAdd(&cls[c], 1)] = it; });
+}
+
 // Scale bound of every new work item (the P2G fixed-point scale), from the
 // freshly gathered particles.
 __global__ __launch_bounds__(WG) void k_item_bounds(SortArgs a)
@@ -544,11 +615,15 @@ hipError_t launch_sort(const SortArgs &a, const StateRows *rows, int *flags, hip
         if (wide) k_keys<SORT_PER><<<gS, WG, 0, st>>>(a);
         else k_keys<1><<<gS, WG, 0, st>>>(a);
     }
-    k_dilate<<<gT, WG, 0, st>>>(a);
-    k_scan_tiles<<<ntiles, WG, 0, st>>>(a);
-    k_scan_top<<<1, WG, 0, st>>>(a, ntiles);
-    k_scan_emit<<<ntiles, WG, 0, st>>>(a);
-    k_item_order<<<1, 1024, 0, st>>>(a);
+    if (a.T <= SMALL_BINS) {
+        k_plan_small<<<1, 1024, 0, st>>>(a);
+    } else {
+        k_dilate<<<gT, WG, 0, st>>>(a);
+        k_scan_tiles<<<ntiles, WG, 0, st>>>(a);
+        k_scan_top<<<1, WG, 0, st>>>(a, ntiles);
+        k_scan_emit<<<ntiles, WG, 0, st>>>(a);
+        k_item_order<<<1, 1024, 0, st>>>(a);
+    }
     if (a.N > 0) {
         const int gN8 = (gN + 7) & ~7;    // xcd_remap (gather) needs a multiple of 8 workgroups
         if (wide) k_scatter<SORT_PER><<<gS, WG, 0, st>>>(a);
