@@ -1610,9 +1610,8 @@ __global__ __launch_bounds__(NT, 4) void k_g2p(StepArgs a)
 // leave, and keeps the prefetch.
 // Bound by vector instructions (83 to 87 % of the cycles issue one at 256
 // scenes): what it gained came from fewer of them, the strain series in scalar
-// invariants and the wave-wide slow paths (100 substeps of 256 scenes of
-// 8,000 particles 44.1 -> 40.5 ms, of 23 scenes 2.84 -> 2.52 ms with the same
-// changes in the separate kernels).
+// invariants and the wave-wide slow paths (100 substeps of 256 scenes, 7.7
+// million particles, 44.1 -> 40.5 ms; 50 of 23 scenes 2.84 -> 2.52 ms).
 template <int B, bool PEN, int NT>
 __global__ __launch_bounds__(NT, 4) void k_g2p2g(StepArgs a)
 {
