@@ -562,7 +562,7 @@ __device__ __forceinline__ void init_particle(const SceneDev *scenes, int s, con
 #pragma unroll
     for (int e = 0; e < 9; e++) G[e] = F[e] - (e % 4 == 0 ? 1.0f : 0.0f);
     int bad = 0;
-    stress_of(G, mat, tau, bad);
+    state_stress(G, mat, tau, bad);
     float chk = 0.0f;   // NaN or infinity in any input makes it fail the test below
 #pragma unroll
     for (int d = 0; d < 3; d++) {
@@ -1919,9 +1919,9 @@ __global__ __launch_bounds__(WG) void k_get_state(const SceneDev *scenes, const 
         const float mass = S.mass, kstress = S.kstress;
         float tau[9];
         int bad = 0;
-        stress_of(G, mat, tau, bad);
+        state_stress(G, mat, tau, bad);
 #pragma unroll
-        for (int e = 0; e < 9; e++) A[e] = (A[e] + kstress * tau[e]) / mass;
+        for (int e = 0; e < 9; e++) A[e] = fmaf(kstress, tau[e], A[e]) / mass;
         store_row(C + 9 * k, A);
     }
     if (x) store_row(x + 3 * k, xr);

@@ -265,20 +265,44 @@ MPM_HD void tau_from_M(const float *G, const float *M, float tau[9])
         }
 }
 
+// The arithmetic of the kernels that take a state in and give it out is written
+// out, sums of products included (state_stress below says why).
+#if defined(__clang__)
+#define MPM_NO_CONTRACT _Pragma("clang fp contract(off)")
+#else
+#define MPM_NO_CONTRACT
+#endif
+
+MPM_HD void state_right_strain(const float *G, Sym3 &s)
+{
+    MPM_NO_CONTRACT
+    s.a00 = 2.0f * G[0] + (G[6] * G[6] + (G[0] * G[0] + G[3] * G[3]));
+    s.a11 = 2.0f * G[4] + (G[7] * G[7] + (G[1] * G[1] + G[4] * G[4]));
+    s.a22 = 2.0f * G[8] + (G[8] * G[8] + (G[2] * G[2] + G[5] * G[5]));
+    s.a01 = (G[1] + G[3]) + fmaf(G[6], G[7], fmaf(G[0], G[1], G[3] * G[4]));
+    s.a02 = (G[2] + G[6]) + fmaf(G[6], G[8], fmaf(G[0], G[2], G[3] * G[5]));
+    s.a12 = (G[5] + G[7]) + fmaf(G[7], G[8], fmaf(G[1], G[2], G[4] * G[5]));
+}
+
 // Hencky elasticity with an optional von Mises return map through the
 // eigen-decomposition of F^T F (any state).  Gt is the trial displacement
 // gradient; Gout receives the projected one, tau the Kirchhoff stress of Gout.
-// Returns 1 if the particle yielded.
+// Returns 1 if the particle yielded.  STATE: the roundings of state_stress below.
+template <bool STATE = false>
 MPM_HD int hencky_eigen(const float *Gt, const Material &mat, float *Gout, float tau[9], int &bad)
 {
     const float SMIN = 1e-6f;
     Sym3 s;   // C - I = G + G^T + G^T G
-    s.a00 = 2.0f * Gt[0] + (Gt[0] * Gt[0] + Gt[3] * Gt[3] + Gt[6] * Gt[6]);
-    s.a11 = 2.0f * Gt[4] + (Gt[1] * Gt[1] + Gt[4] * Gt[4] + Gt[7] * Gt[7]);
-    s.a22 = 2.0f * Gt[8] + (Gt[2] * Gt[2] + Gt[5] * Gt[5] + Gt[8] * Gt[8]);
-    s.a01 = Gt[1] + Gt[3] + (Gt[0] * Gt[1] + Gt[3] * Gt[4] + Gt[6] * Gt[7]);
-    s.a02 = Gt[2] + Gt[6] + (Gt[0] * Gt[2] + Gt[3] * Gt[5] + Gt[6] * Gt[8]);
-    s.a12 = Gt[5] + Gt[7] + (Gt[1] * Gt[2] + Gt[4] * Gt[5] + Gt[7] * Gt[8]);
+    if (STATE) {
+        state_right_strain(Gt, s);
+    } else {
+        s.a00 = 2.0f * Gt[0] + (Gt[0] * Gt[0] + Gt[3] * Gt[3] + Gt[6] * Gt[6]);
+        s.a11 = 2.0f * Gt[4] + (Gt[1] * Gt[1] + Gt[4] * Gt[4] + Gt[7] * Gt[7]);
+        s.a22 = 2.0f * Gt[8] + (Gt[2] * Gt[2] + Gt[5] * Gt[5] + Gt[8] * Gt[8]);
+        s.a01 = Gt[1] + Gt[3] + (Gt[0] * Gt[1] + Gt[3] * Gt[4] + Gt[6] * Gt[7]);
+        s.a02 = Gt[2] + Gt[6] + (Gt[0] * Gt[2] + Gt[3] * Gt[5] + Gt[6] * Gt[8]);
+        s.a12 = Gt[5] + Gt[7] + (Gt[1] * Gt[2] + Gt[4] * Gt[5] + Gt[7] * Gt[8]);
+    }
     float V[9];
     sym_eig(s, V);
     float lam[3] = {s.a00, s.a11, s.a22};
@@ -604,6 +628,98 @@ MPM_HD void stress_of(const float *G, const Material &mat, float tau[9], int &ba
     m2.plastic = 0;
     float Gc[9];
     hencky_update<true>(G, m2, Gc, tau, bad);
+}
+
+// stress_of for the kernels that take a state in and give it out.  They undo
+// each other (A = m C - k tau on the way in, C = (A + k tau) / m on the way out),
+// so C survives to the last bit, whichever of them took the state in, only if all
+// of them round alike.  The roundings are therefore written out: left to the
+// compiler, products that two of a kernel's branches share are formed before
+// them, and which of a sum's products is fused follows from that (0.1 % of C in
+// the last bit, and 1e-3 of a network output whose inputs are rounded to BF16).
+// The strain b - I: the order of the fused sums is the one these kernels were
+// first compiled to, and differs between the entries and the two models.
+MPM_HD void state_neo_hookean(const float *G, float mu, float la, float tau[9], int &bad)
+{
+    MPM_NO_CONTRACT
+    const float jm1 = det_minus_one(G);
+    bad |= !(jm1 > -1.0f);
+    const float l = la * flog1p(jm1);
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = i; j < 3; j++) {
+            const float *a = G + 3 * i, *b = G + 3 * j;
+            const float ggt = fmaf(a[2], b[2], fmaf(a[0], b[0], a[1] * b[1]));
+            const float s = i == j ? fmaf(2.0f, a[i], ggt) : (a[j] + b[i]) + ggt;
+            tau[3 * i + j] = tau[3 * j + i] = i == j ? fmaf(mu, s, l) : mu * s;
+        }
+}
+
+// hencky_series_strain without a yield test.
+MPM_HD int state_hencky_series(const float *G, float e[6])
+{
+    MPM_NO_CONTRACT
+    float s[6];
+    s[0] = fmaf(2.0f, G[0], fmaf(G[2], G[2], fmaf(G[0], G[0], G[1] * G[1])));
+    s[1] = fmaf(2.0f, G[4], fmaf(G[5], G[5], fmaf(G[4], G[4], G[3] * G[3])));
+    s[2] = fmaf(2.0f, G[8], fmaf(G[8], G[8], fmaf(G[6], G[6], G[7] * G[7])));
+    s[3] = (G[1] + G[3]) + fmaf(G[2], G[5], fmaf(G[1], G[4], G[0] * G[3]));
+    s[4] = (G[2] + G[6]) + fmaf(G[2], G[8], fmaf(G[0], G[6], G[1] * G[7]));
+    s[5] = (G[5] + G[7]) + fmaf(G[5], G[8], fmaf(G[3], G[6], G[4] * G[7]));
+    const float nb2 = fmaf(2.0f, fmaf(s[5], s[5], fmaf(s[3], s[3], s[4] * s[4])),
+                           fmaf(s[2], s[2], fmaf(s[0], s[0], s[1] * s[1])));
+    const float a = 2.0f + s[0], d = 2.0f + s[1], f = 2.0f + s[2];
+    float inv[6], z[6], z2[6], p[6], q[6];
+    inv[0] = fmaf(d, f, -(s[5] * s[5]));
+    inv[1] = fmaf(a, f, -(s[4] * s[4]));
+    inv[2] = fmaf(a, d, -(s[3] * s[3]));
+    inv[3] = fmaf(s[4], s[5], -(s[3] * f));
+    inv[4] = fmaf(s[3], s[5], -(s[4] * d));
+    inv[5] = fmaf(s[3], s[4], -(a * s[5]));
+    const float idet = frcp(fmaf(s[4], inv[4], fmaf(a, inv[0], s[3] * inv[3])));
+#pragma unroll
+    for (int k = 0; k < 6; k++) inv[k] *= idet;
+    sym_mul(s, inv, z);
+    sym_mul(z, z, z2);
+#pragma unroll
+    for (int k = 0; k < 6; k++) p[k] = fmaf(z2[k], 1.0f / 9.0f, k < 3 ? 1.0f / 7.0f : 0.0f);
+    sym_mul(z2, p, q);
+#pragma unroll
+    for (int k = 0; k < 6; k++) p[k] = q[k] + (k < 3 ? 1.0f / 5.0f : 0.0f);
+    sym_mul(z2, p, q);
+#pragma unroll
+    for (int k = 0; k < 6; k++) p[k] = q[k] + (k < 3 ? 1.0f / 3.0f : 0.0f);
+    sym_mul(z2, p, q);
+#pragma unroll
+    for (int k = 0; k < 6; k++) p[k] = q[k] + (k < 3 ? 1.0f : 0.0f);
+    sym_mul(z, p, e);
+    return nb2 <= 0.1225f && det_minus_one(G) > -0.5f;
+}
+
+// Each particle takes the series or the eigen-decomposition by its own state
+// alone: with one path per wave, as in hencky_update, its stress would follow
+// the particles it shares a wave with, hence the order they are stored in.
+MPM_HD void state_stress(const float *G, const Material &mat, float tau[9], int &bad)
+{
+    if (mat.model == 0) {
+        state_neo_hookean(G, mat.mu, mat.la, tau, bad);
+        return;
+    }
+    if (mat.model == 2) {
+        float Gc[9];
+        fluid_update(G, mat, Gc, tau, bad);
+        return;
+    }
+    float e[6];
+    if (state_hencky_series(G, e)) {
+        hencky_tau_of_strain(e, mat, tau);
+        return;
+    }
+    Material m2 = mat;
+    m2.plastic = 0;
+    float Gc[9];
+    hencky_eigen<true>(G, m2, Gc, tau, bad);
 }
 
 // ---------------------------------------------------------------- rotations and SDFs
