@@ -35,9 +35,10 @@ namespace {
 constexpr int STAGE_RING = 4;
 
 struct GraphKey {
-    int parity, since_sort, sort_every;
+    int parity, since_sort, sort_every, cut;
     bool operator<(const GraphKey &o) const
     {
+        if (cut != o.cut) return cut < o.cut;
         if (parity != o.parity) return parity < o.parity;
         if (since_sort != o.since_sort) return since_sort < o.since_sort;
         return sort_every < o.sort_every;
@@ -106,6 +107,7 @@ struct mpm_ctx_s {
 
     // library-owned surrogate (mpm_surrogate_load / mpm_step_blocks): network and per-block arrays
     mpm::SurNet *net = nullptr;
+    bool whole_items = false;        // blocks cut to MPM_OPT_CHUNK only (see whole_items_from_now)
     int *d_sb_box = nullptr, *d_sb_origin = nullptr;
     float *d_sb_feat = nullptr, *d_sb_grid0 = nullptr, *d_sb_pred = nullptr, *d_sb_res = nullptr;
     long long sb_nodes = 0;          // box nodes the per-block arrays hold
@@ -357,8 +359,19 @@ hipError_t resolve_timing(mpm_ctx ctx)
 int cut_of(mpm_ctx ctx)
 {
     if (ctx->persistent) return ctx->CH;   // its grid barriers cost per workgroup
+    if (ctx->whole_items) return ctx->CH;
     const long long per_cu = ((long long)ctx->N + ctx->cus - 1) / ctx->cus;
     return (int)std::min<long long>(ctx->CH, std::max<long long>((per_cu + 63) / 64 * 64, 64));
+}
+
+// A surrogate's input is rounded to BF16: a node sum that turns in its last bit is
+// 1e-3 of a network output where it crosses a rounding boundary.  The pieces of a
+// cut block add to a node in any order, each with a fixed-point scale of its own,
+// so a context that feeds a surrogate keeps its blocks whole.
+void whole_items_from_now(mpm_ctx ctx)
+{
+    if (cut_of(ctx) < ctx->CH) ctx->since_sort = 1 << 30;   // the present items are pieces
+    ctx->whole_items = true;
 }
 
 SortArgs sort_args(mpm_ctx ctx)
@@ -513,7 +526,7 @@ mpm_status queue_plain(mpm_ctx ctx, int n)
 // (captured on first use for the current buffer parity and sort phase).
 mpm_status queue_graph_block(mpm_ctx ctx)
 {
-    GraphKey key{ctx->cur, std::min(ctx->since_sort, ctx->sort_every), ctx->sort_every};
+    GraphKey key{ctx->cur, std::min(ctx->since_sort, ctx->sort_every), ctx->sort_every, cut_of(ctx)};
     auto it = ctx->graphs.find(key);
     if (it == ctx->graphs.end()) {
         const int cur0 = ctx->cur, ss0 = ctx->since_sort;
@@ -1242,6 +1255,7 @@ mpm_status mpm_sur_features(mpm_ctx ctx, float *feat, int cf, float *grid0, cons
     const int R = common_res(ctx);
     ARGCHK(R > 0, "the surrogate needs one grid resolution for all scenes");
     hipSetDevice(ctx->dev);
+    whole_items_from_now(ctx);
     if (ctx->since_sort >= ctx->sort_every) {   // due, or the state was set: work lists and scatter bounds
         mpm_status st = do_sort(ctx);
         if (st != MPM_OK) return st;
@@ -1373,6 +1387,7 @@ mpm_status mpm_surrogate_load(mpm_ctx ctx, const void *weights, size_t bytes)
     }
     mpm::surnet_destroy(ctx->net);
     ctx->net = net;
+    whole_items_from_now(ctx);
     return MPM_OK;
 }
 

@@ -24,11 +24,11 @@ def mpm():
     return m
 
 
-def _scene(seed, model):
+def _scene(seed, model, per_block=PER_BLOCK):
     rng = np.random.default_rng(seed)
     blocks = np.array([(i, j, k) for i in (1, 4) for j in (1, 4) for k in (1, 4)])
-    x = (blocks[:, None, :] * 4 + 0.5 + rng.uniform(0.01, 3.99, size=(8, PER_BLOCK, 3))) / RES
-    n = 8 * PER_BLOCK
+    x = (blocks[:, None, :] * 4 + 0.5 + rng.uniform(0.01, 3.99, size=(8, per_block, 3))) / RES
+    n = 8 * per_block
     order = rng.permutation(n)                       # creation order: the blocks' particles mixed
     x = x.reshape(n, 3)[order].astype(np.float32)
     F = np.eye(3) + rng.choice([0.01, 0.06, 0.15], n)[:, None, None] * rng.normal(size=(n, 3, 3))
@@ -39,8 +39,8 @@ def _scene(seed, model):
 
 def _features(sim):
     import torch
-    feat = torch.zeros((2, RES, RES, RES, 8), device="cuda")
-    grid0 = torch.zeros((2, RES, RES, RES, 4), device="cuda")
+    feat = torch.zeros((len(sim.scenes), RES, RES, RES, 8), device="cuda")
+    grid0 = torch.zeros((len(sim.scenes), RES, RES, RES, 4), device="cuda")
     torch.cuda.synchronize()
     sim.sur_features(feat, grid0)
     assert sim.sync() == 0
@@ -68,3 +68,25 @@ def test_state_bits_do_not_follow_the_route(mpm, model):
         for name, a, b in zip(("C", "C after the sort", "features", "node sums"), got[0], other):
             np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32), err_msg=name)
     np.testing.assert_array_equal(got[0][0], got[0][1])
+
+
+@pytest.mark.parametrize("chunk", [128, 2048])
+def test_surrogate_input_does_not_follow_the_batch(mpm, chunk):
+    """A small context cuts its blocks to the number of CUs, a large one does not: the
+    network's input of a scene is the same in both, and from call to call, as long as
+    its blocks fit the chunk."""
+    announce("surrogate input", chunk)
+    small = [_scene(3, scenes.HENCKY_VM, per_block=120)]
+    filler = _scene(4, scenes.HENCKY_VM, per_block=4 * chunk * 256 // 8 // 3)
+    got = []
+    for made in (small, small + [filler], small):
+        sim = mpm.Sim([sc for sc, _ in made])
+        sim.set_option(mpm.OPT_CHUNK, chunk)
+        sim.set_state(*(np.concatenate([st[k] for _, st in made]) for k in range(4)))
+        for _ in range(2):
+            feat, grid0 = _features(sim)
+            got.append((feat[0], grid0[0]))
+        sim.close()
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
