@@ -690,11 +690,13 @@ __device__ __forceinline__ void queue_block(const GridOut &o, int s, int bin_off
     }
 }
 
-// Quadratic B-spline weight of node o (0, 1, 2) for the offset f in [0.5, 1.5).
+// Quadratic B-spline weight of node o (0, 1, 2) for the offset f: bspline_w's
+// polynomials, for any f (a particle past the grid's edge has a clamped base
+// cell and an offset outside [0.5, 1.5); its weights still sum to 1).
 __device__ __forceinline__ float bspline_at(float f, float o)
 {
-    const float u = f - o, e = 1.5f - fabsf(u);
-    return o == 1.0f ? 0.75f - u * u : 0.5f * e * e;
+    const float e = o == 0.0f ? 1.5f - f : f - 0.5f, b = f - 1.0f;
+    return o == 1.0f ? 0.75f - b * b : 0.5f * e * e;
 }
 
 // Slow path of P2G: scatter one particle straight into the global grid and
