@@ -344,7 +344,7 @@ struct ConvPlan {
     int HZ, HY, HX;                // halo extents
     int tiles_x, tiles_y, tiles_z, ntiles, nco;
     unsigned mTX, mHX, mHY;        // reciprocals ceil(2^32 / d)
-    int x16, lds;
+    int x16, wide, lds;            // 16-byte copies possible; boxes of over 2^32 voxels
 };
 
 template <int NF, int KIND, int FR>
@@ -390,6 +390,7 @@ __global__ __launch_bounds__((NF == 2 && FR == 8 ? 8 : 16) * 64) void k_conv_pos
 #pragma unroll
         for (int n = 0; n < NF; n++) acc[f][n] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     const int kc = a.cin / 32, nft = (a.cout + 15) / 16, ns = 4 * p.HZ * p.HY * p.HX;
+    const VoxelIndex xi(a.ih, a.iw, a.cx, p.wide);
     const uint16_t *xb = a.x + (size_t)bn * a.id * a.ih * a.iw * a.cx + a.x_off;
     for (int c = 0; c < kc; c++) {
         for (int s0 = 64 * wv; s0 < ns; s0 += nt) {
@@ -401,7 +402,7 @@ __global__ __launch_bounds__((NF == 2 && FR == 8 ? 8 : 16) * 64) void k_conv_pos
             const int gz = hz0 + lz, gy = hy0 + ly, gx = hx0 + lx;
             const bool in = gz >= 0 && gy >= 0 && gx >= 0 && gz < a.id && gy < a.ih && gx < a.iw;
             const uint16_t *src =
-                in ? xb + (size_t)(unsigned)((gz * a.ih + gy) * a.iw + gx) * a.cx + 32 * c + c8 : g_zero_piece;
+                in ? xb + xi(gz, gy, gx) + 32 * c + c8 : g_zero_piece;
             if (p.x16) __builtin_amdgcn_global_load_lds((glob_void *)src, (lds_void *)(halo + s0), 16, 0, 0);
             else halo[s] = load_piece(src, 8);
         }
@@ -479,6 +480,7 @@ __global__ __launch_bounds__(256) void k_conv_first(ConvArgs a, ConvPlan p)
     const int y0 = (b % p.tiles_y) * FR;
     b /= p.tiles_y;
     const int z0 = (b % p.tiles_z) * p.TZ, bn = b / p.tiles_z;
+    const VoxelIndex xi(a.ih, a.iw, a.cx, p.wide);
     const uint16_t *xb = a.x + (size_t)bn * a.id * a.ih * a.iw * a.cx + a.x_off;
     const int nh = p.HZ * HY * p.HX;
     for (int s0 = 64 * wv; s0 < nh; s0 += 256) {
@@ -487,7 +489,7 @@ __global__ __launch_bounds__(256) void k_conv_first(ConvArgs a, ConvPlan p)
         const int q = div_by(v, p.mHX, p.HX), lx = v - q * p.HX, lz = q / HY, ly = q - lz * HY;
         const int gz = z0 - 1 + lz, gy = y0 - 1 + ly, gx = x0 - 1 + lx;
         const bool in = gz >= 0 && gy >= 0 && gx >= 0 && gz < a.id && gy < a.ih && gx < a.iw;
-        const uint16_t *src = in ? xb + (size_t)(unsigned)((gz * a.ih + gy) * a.iw + gx) * a.cx : g_zero_piece;
+        const uint16_t *src = in ? xb + xi(gz, gy, gx) : g_zero_piece;
         __builtin_amdgcn_global_load_lds((glob_void *)src, (lds_void *)(halo + s0), 16, 0, 0);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copies are not tracked by the compiler
@@ -620,7 +622,7 @@ struct WgradPlan {
     int tiles_x, tiles_y, tiles_z, ntiles, tpg, groups, nvar;
     unsigned mTX, mHX, mNP;        // reciprocals ceil(2^32 / d) of TX, HX and 32 ns
     int g_off, x_off, lds;         // byte offsets of the G and X tiles, LDS bytes
-    int x16, g16;                  // 16-byte copies possible
+    int x16, g16, wide;            // 16-byte copies possible; boxes of over 2^32 voxels
 };
 
 typedef __attribute__((address_space(3))) s4 lds_s4;
@@ -671,7 +673,8 @@ __global__ __launch_bounds__(256, 3) void k_wgrad(WgradArgs a, WgradPlan p)
     // 32-byte channel chunks are swizzled so that the four voxels of a 16-lane group hit distinct banks
     const int gsw = GP == 8 ? j : (GP == 4 ? j >> 1 : 0);
     const int nx = p.TZ * RY * p.HX * XP, ng = WTY * npos * GP;
-    const int tile_end = min(p.ntiles, (group + 1) * p.tpg);
+    const VoxelIndex xi(a.ih, a.iw, a.cx, p.wide), gi(a.oh, a.ow, a.cg, p.wide);
+    const int tile_end = (int)min((long long)p.ntiles, (group + 1LL) * p.tpg);
     for (int tile = group * p.tpg; tile < tile_end; tile++) {
         int b = tile;
         const int x0 = (b % p.tiles_x) * p.TX;
@@ -700,7 +703,7 @@ __global__ __launch_bounds__(256, 3) void k_wgrad(WgradArgs a, WgradPlan p)
                 in = gz >= 0 && gy >= 0 && gx >= 0 && gz < a.id && gy < a.ih && gx < a.iw;
             }
             in &= ci0 + c8 < a.cin;
-            const uint16_t *src = in ? xb + (size_t)(unsigned)((gz * a.ih + gy) * a.iw + gx) * a.cx + c8 : g_zero_piece;
+            const uint16_t *src = in ? xb + xi(gz, gy, gx) + c8 : g_zero_piece;
             if (p.x16) __builtin_amdgcn_global_load_lds((glob_void *)src, (lds_void *)(sm + p.x_off + 16 * s0), 16, 0, 0);
             else *(uint4 *)(sm + p.x_off + 16 * s) = load_piece(src, 8);
         }
@@ -712,7 +715,7 @@ __global__ __launch_bounds__(256, 3) void k_wgrad(WgradArgs a, WgradPlan p)
             const int c8 = 8 * (GP == 8 ? ph ^ ((pos & 3) << 1) : (GP == 4 ? ph ^ (pos & 2) : ph));
             const int gz = z0 + z, gy = y0 + yo, gx = x0 + x, left = a.cout - co0 - c8;
             const bool in = pos < nreal && gz < a.od && gy < a.oh && gx < a.ow && left > 0;
-            const uint16_t *src = in ? gb + (size_t)(unsigned)((gz * a.oh + gy) * a.ow + gx) * a.cg + c8 : g_zero_piece;
+            const uint16_t *src = in ? gb + gi(gz, gy, gx) + c8 : g_zero_piece;
             if (p.g16) __builtin_amdgcn_global_load_lds((glob_void *)src, (lds_void *)(sm + p.g_off + 16 * s0), 16, 0, 0);
             else *(uint4 *)(sm + p.g_off + 16 * s) = load_piece(src, in ? min(left, 8) : 8);
         }
@@ -1381,6 +1384,7 @@ static bool conv_plan(const ConvArgs &a, int NF, ConvPlan &p, int &FR)
     p.mTX = recip(p.TX);
     p.mHX = recip(p.HX);
     p.mHY = recip(p.HY);
+    p.wide = VoxelIndex::needs_wide(a.id, a.ih, a.iw);
     p.x16 = a.cx % 8 == 0 && a.x_off % 8 == 0 && ((uintptr_t)a.x & 15) == 0;
     return true;
 }
@@ -1439,6 +1443,7 @@ static bool first_plan(const ConvArgs &a, ConvPlan &p)
     p.mTX = recip(p.TX);
     p.mHX = recip(p.HX);
     p.lds = 16 * p.HZ * p.HY * p.HX;
+    p.wide = VoxelIndex::needs_wide(a.id, a.ih, a.iw);
     return true;
 }
 
@@ -1578,6 +1583,7 @@ static bool wgrad_plan(const WgradArgs &a, WgradPlan &p)
     p.ntiles = (int)ntiles;
     p.tpg = (int)tpg;
     p.groups = (int)groups;
+    p.wide = VoxelIndex::needs_wide(a.id, a.ih, a.iw) || VoxelIndex::needs_wide(a.od, a.oh, a.ow);
     p.x16 = a.cx % 8 == 0 && a.x_off % 8 == 0 && ((uintptr_t)a.x & 15) == 0;
     p.g16 = a.cg % 8 == 0 && a.g_off % 8 == 0 && a.cout % 8 == 0 && ((uintptr_t)a.g & 15) == 0;
     return true;

@@ -35,6 +35,21 @@ struct WgradArgs {
     int accumulate;
 };
 
+// Elements from a box's first voxel to voxel (z, y, x) of an [id][ih][iw][c]
+// tensor.  Boxes of up to 2^32 voxels count them in 32 bits (64 bits throughout:
+// 1 % of a weight gradient); the branch is the same for a whole launch.
+struct VoxelIndex {
+    unsigned h, w, c;
+    bool wide;
+    __host__ __device__ VoxelIndex(int ih, int iw, int c_, bool wide_) : h((unsigned)ih), w((unsigned)iw), c((unsigned)c_), wide(wide_) {}
+    static bool needs_wide(int id, int ih, int iw) { return (unsigned long long)id * ih > 0xffffffffull / iw; }
+    __host__ __device__ size_t operator()(int z, int y, int x) const
+    {
+        if (wide) return (((size_t)(unsigned)z * h + (unsigned)y) * w + (unsigned)x) * c;
+        return (size_t)(((unsigned)z * h + (unsigned)y) * w + (unsigned)x) * c;
+    }
+};
+
 hipError_t conv(const ConvArgs &a, hipStream_t st);
 // One tensor's weights to pack, as k_pack's comment has it.
 struct PackJob {
