@@ -695,8 +695,8 @@ __device__ __forceinline__ void queue_block(const GridOut &o, int s, int bin_off
 // cell and an offset outside [0.5, 1.5); its weights still sum to 1).
 __device__ __forceinline__ float bspline_at(float f, float o)
 {
-    const float e = o == 0.0f ? 1.5f - f : f - 0.5f, b = f - 1.0f;
-    return o == 1.0f ? 0.75f - b * b : 0.5f * e * e;
+    const float u = f - o, e = fmaf(o - 1.0f, u, 1.5f);
+    return o == 1.0f ? 0.75f - u * u : 0.5f * e * e;
 }
 
 // Slow path of P2G: scatter one particle straight into the global grid and
