@@ -163,13 +163,15 @@ __global__ __launch_bounds__(WG) void k_dilate(SortArgs a)
 static constexpr int SCAN_PER = 8;
 static constexpr int SCAN_TILE = WG * SCAN_PER;
 
-// Particles per item of a block with c of them.  Blocks are cut to a.cut, but
-// not where they hold over 12 particles a cell: there the largest sum a node of
-// the item can reach sets the P2G's fixed-point scale, a shorter item would get
-// a finer one, and the rounding of its terms would follow the launch
-// configuration (6,000 fluid particles at 40 a cell: velocity gradients moved by
-// 2e-5).  Up to there the limit of the single term sets the scale, whatever the
-// item's length.
+// Particles per item of a block with c of them: a.cut, or a.CH where the block
+// holds over 12 particles a cell.  An item's P2G takes its fixed-point scale from
+// its own scatter bound and fullest cell, so a piece has a finer scale than its
+// block, and the rounding of its terms follows the launch configuration.  In
+// dense material that shows (6,000 fluid particles at 40 a cell: velocity
+// gradients moved by 2e-5, 6,360 -> 3,160 us); where the single term's limit sets
+// the scale (up to about 20 particles in the fullest cell) it is the last bit of
+// the block's largest term.  The mean is a heuristic for that: a half-filled block
+// of dense material is below the line and is cut.
 __device__ __forceinline__ int item_size(const SortArgs &a, int c)
 {
     return c <= 12 * a.B * a.B * a.B ? a.cut : a.CH;
@@ -432,12 +434,16 @@ __global__ __launch_bounds__(WG) void k_gather(SortArgs a)
 // eighth item of the order), and items range from a few dozen particles to
 // a full chunk: in block order the largest ones could start last and hold
 // the end of the launch.  A counting sort by particle count in 64 classes
-// (order inside a class: arbitrary).
+// (order inside a class: arbitrary).  Where blocks are cut below the chunk, half
+// of the classes are for the items up to the cut, half for the whole blocks past
+// it: 64 classes of the chunk would put the pieces of a small context into one.
 constexpr int ORDER_CLASSES = 64;
 
-__device__ __forceinline__ int order_class(int count, int CH)
+__device__ __forceinline__ int order_class(const SortArgs &a, int count)
 {
-    return min(ORDER_CLASSES - 1, (int)((long long)count * ORDER_CLASSES / (CH + 1)));
+    constexpr int H = ORDER_CLASSES / 2;
+    if (a.cut >= a.CH) return min(ORDER_CLASSES - 1, (int)((long long)count * ORDER_CLASSES / (a.CH + 1)));
+    return count <= a.cut ? count * H / (a.cut + 1) : H + (count - a.cut - 1) * H / (a.CH - a.cut);
 }
 
 __global__ __launch_bounds__(1024) void k_item_order(SortArgs a)
@@ -446,7 +452,7 @@ __global__ __launch_bounds__(1024) void k_item_order(SortArgs a)
     const int n = *a.L.n_items;
     if (threadIdx.x < ORDER_CLASSES) cnt[threadIdx.x] = 0;
     __syncthreads();
-    for (int it = threadIdx.x; it < n; it += blockDim.x) atomicAdd(&cnt[order_class(a.L.items[it].count, a.CH)], 1);
+    for (int it = threadIdx.x; it < n; it += blockDim.x) atomicAdd(&cnt[order_class(a, a.L.items[it].count)], 1);
     __syncthreads();
     if (threadIdx.x == 0) {
         int s = 0;   // classes from the largest down: cnt[c] becomes the first slot of class c
@@ -458,7 +464,7 @@ __global__ __launch_bounds__(1024) void k_item_order(SortArgs a)
     }
     __syncthreads();
     for (int it = threadIdx.x; it < n; it += blockDim.x)
-        a.L.order[atomicAdd(&cnt[order_class(a.L.items[it].count, a.CH)], 1)] = it;
+        a.L.order[atomicAdd(&cnt[order_class(a, a.L.items[it].count)], 1)] = it;
 }
 
 // k_dilate, the three scan kernels and k_item_order in one workgroup, for few
@@ -501,7 +507,7 @@ __global__ __launch_bounds__(1024) void k_plan_small(SortArgs a)
 #pragma unroll
         for (int i = 0; i < SMALL_PER; i++) {
             const int ch = item_size(a, v[i].x);
-            for (int c = 0; c < v[i].y; c++, it++) f(it, order_class(min(ch, v[i].x - c * ch), a.CH));
+            for (int c = 0; c < v[i].y; c++, it++) f(it, order_class(a, min(ch, v[i].x - c * ch)));
         }
     };
     own_items([&](int, int c) { atomicAdd(&cls[c], 1); });
