@@ -9,7 +9,6 @@
 namespace {
 
 int taps_of(int kind) { return kind == 0 || kind == 1 ? 27 : (kind == 2 ? 8 : 1); }
-constexpr int JOBS_AT_ONCE = 48;   // tensors of one pack or Adam launch
 int ceil16(int c) { return (c + 15) / 16 * 16; }
 int st_of(hipError_t e) { return e == hipSuccess ? 0 : -2; }
 bool kind_ok(int k) { return k >= 0 && k <= 3; }
@@ -90,9 +89,10 @@ int mpm_nn_pack_many(int count, const float *const *w, const int *kind, const in
     if (count <= 0 || !w || !kind || !w_cin || !cin || !cout || !transpose || !out) return -1;
     for (int i = 0; i < count; i++)
         if (!w[i] || !out[i] || !kind_ok(kind[i]) || cin[i] <= 0 || cout[i] <= 0 || w_cin[i] < cin[i]) return -1;
-    nn::PackJob jobs[JOBS_AT_ONCE];
-    for (int i = 0; i < count; i += JOBS_AT_ONCE) {
-        const int n = count - i < JOBS_AT_ONCE ? count - i : JOBS_AT_ONCE;
+    constexpr int MAX = nn::Jobs<nn::PackJob>::MAX;   // tensors of one launch
+    nn::PackJob jobs[MAX];
+    for (int i = 0; i < count; i += MAX) {
+        const int n = count - i < MAX ? count - i : MAX;
         for (int j = 0; j < n; j++) {
             const int k = i + j, ci_e = transpose[k] ? cout[k] : cin[k], co_e = transpose[k] ? cin[k] : cout[k];
             jobs[j] = nn::pack_job(w[k], taps_of(kind[k]), w_cin[k], cin[k], cout[k], ceil16(ci_e), ceil16(co_e),
@@ -204,9 +204,10 @@ int mpm_nn_adam_many(int count, float *const *p, const float *const *g, float *c
     if (count <= 0 || !p || !g || !m || !v || !n || t < 1) return -1;
     for (int i = 0; i < count; i++)
         if (!p[i] || !g[i] || !m[i] || !v[i] || n[i] <= 0) return -1;
-    nn::AdamJob jobs[JOBS_AT_ONCE];
-    for (int i = 0; i < count; i += JOBS_AT_ONCE) {
-        const int c = count - i < JOBS_AT_ONCE ? count - i : JOBS_AT_ONCE;
+    constexpr int MAX = nn::Jobs<nn::AdamJob>::MAX;
+    nn::AdamJob jobs[MAX];
+    for (int i = 0; i < count; i += MAX) {
+        const int c = count - i < MAX ? count - i : MAX;
         for (int j = 0; j < c; j++) {
             const int k = i + j;
             const uintptr_t bits = (uintptr_t)p[k] | (uintptr_t)g[k] | (uintptr_t)m[k] | (uintptr_t)v[k];

@@ -158,10 +158,9 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a, int ncg)
         src[f] = a.x + (((((long long)nn * a.id + ks * z) * a.ih + ks * y) * a.iw + ks * x) * a.cx + a.x_off + 4 * g);
     }
     const uint16_t *w = a.w + (size_t)cn * 256 + 4 * lane;
-#pragma unroll 2
     for (int t = 0; t < ntap; t++) {
         const long long off = (((long long)(t / (ks * ks)) * a.ih + (t / ks) % ks) * a.iw + t % ks) * a.cx;
-#pragma unroll
+#pragma unroll KC ? KC : 1
         for (int c = 0; c < kc; c++) {
             s4 A[MF];
 #pragma unroll
@@ -623,7 +622,7 @@ __global__ __launch_bounds__(256, 3) void k_wgrad(WgradArgs a, WgradPlan p)
     typedef const __attribute__((address_space(1))) void glob_void;
     extern __shared__ uint4 smem[];
     char *sm = (char *)smem;
-    int *tab = (int *)smem;            // per position: byte offset of its X row / 64 << 16 | column
+    int *tab = (int *)smem;            // per position: byte offset of its X row / 32 << 16 | column
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // the variants (z tap, channel blocks) of one group run on one XCD at about the same time (the
     // dispatcher deals workgroups to the eight XCDs in turn), sharing its tiles in that L2
@@ -1038,7 +1037,6 @@ __global__ __launch_bounds__(256) void k_down_dgrad_mfma(const uint16_t *g, int 
     for (int f = 0; f < MF; f++)
 #pragma unroll
         for (int nf = 0; nf < NF; nf++) acc[f][nf] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
     for (int c = 0; c < kc; c++) {
         s4 A[MF];
 #pragma unroll
@@ -1170,7 +1168,7 @@ __global__ void k_masked_mse(const float *pred, int cp, const float *target, con
 
 // Adam on FP32 master parameters (bias-corrected with step t)
 // 1,024 elements per workgroup, 28 bytes each; every parameter tensor of the
-// network in one launch (34 launches of a few microseconds each, with as many
+// network in one launch (30 launches of a few microseconds each, with as many
 // for the weight fragments, were 553 us an update; two are 61).
 __global__ __launch_bounds__(256) void k_adam(Jobs<AdamJob> q, float lr, float b1, float b2, float eps, int t)
 {
@@ -1386,23 +1384,20 @@ PackJob pack_job(const float *w, int ntap, int w_cin, int cin, int cout, int cin
     return {w, out, total, ntap, w_cin, cin, cout, cin_p, cout_p, transpose, k32};
 }
 
-// Launches `count` jobs, Jobs::MAX at a time; size(job): its workgroups.
+// One launch of `count` jobs (Jobs::MAX at most); size(job): its workgroups.
 template <class Job, class Size, class Launch>
 static hipError_t launch_jobs(const Job *jobs, int count, Size size, Launch launch)
 {
-    for (int i = 0; i < count; i += Jobs<Job>::MAX) {
-        Jobs<Job> q;
-        q.count = std::min(count - i, Jobs<Job>::MAX);
-        q.first[0] = 0;
-        for (int j = 0; j < q.count; j++) {
-            q.j[j] = jobs[i + j];
-            q.first[j + 1] = q.first[j] + size(jobs[i + j]);
-        }
-        launch(q, (unsigned)q.first[q.count]);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    if (count > Jobs<Job>::MAX) return hipErrorInvalidValue;
+    Jobs<Job> q;
+    q.count = count;
+    q.first[0] = 0;
+    for (int j = 0; j < count; j++) {
+        q.j[j] = jobs[j];
+        q.first[j + 1] = q.first[j] + size(jobs[j]);
     }
-    return hipSuccess;
+    launch(q, (unsigned)q.first[count]);
+    return hipGetLastError();
 }
 
 hipError_t pack(const PackJob *jobs, int count, hipStream_t st)

@@ -48,7 +48,7 @@ inline unsigned recip(int d) { return (unsigned)((0x100000000ull + d - 1) / d); 
 // (20 a clock), 15 % more with fewer than three workgroups per CU to overlap
 // these phases; or, where few workgroups are in flight, the rounds of one
 // workgroup's own chain (900 clocks of latency per (z, x) tap, 4,500 per
-// chunk).  Fitted to a sweep of 1,500 tiles over ten layers (32 to 128
+// chunk).  Fitted to a sweep of 1,548 tiles over ten layers (32 to 128
 // channels, 8 and 64 boxes of 40 x 24 x 40 and their two coarser levels): the
 // tiles it picks are within 9 % of the fastest of each.
 inline bool conv_plan(const ConvArgs &a, int NF, ConvPlan &p, int &FR)
