@@ -394,13 +394,14 @@ MPM_HD void sym_mul(const float a[6], const float b[6], float c[6])
 // |b - I|_F <= 0.35 the eigenvalues of Z stay within 0.35 / 1.65 and the first
 // term left out is below 4e-9.  The deviatoric norm of e is that of the
 // principal log strains, so the yield test is the eigen path's.
-// Two forms of the series, e (symmetric, as sym_mul's six entries) and 1 when
+// Three forms of the series, e (symmetric, as sym_mul's six entries) and 1 when
 // it applies (det F > 1/2, |b - I|_F in its range, no yield), else 0:
-// hencky_series_strain in matrix products, for every stress that is stored or
-// has to undo a stored one (the affine momentum A = m C - k tau(F) keeps C to
-// the last bits only if one function forms tau on both sides);
-// hencky_invariant_strain for the fused launches, which keep A in registers
-// and are bound by their vector instructions.
+// hencky_series_strain in matrix products, for a stress that is stored or has
+// to undo a stored one (the affine momentum A = m C - k tau(F) keeps C to the
+// last bits only if one series forms tau on both sides); state_hencky_series,
+// the same with every rounding written out, for the kernels that take a state
+// in and give it out (state_stress); hencky_invariant_strain for the fused
+// launches, which keep A in registers and are bound by their vector instructions.
 
 // s = b - I = G + G^T + G G^T
 MPM_HD void left_strain(const float *G, float s[6])
@@ -612,7 +613,7 @@ MPM_HD void fluid_update(const float *Gt, const Material &mat, float *Gout, floa
     }
 }
 
-// Stress of a state without any return map (a state handed in from outside).
+// Stress of a state without any return map (the start of a surrogate's control step).
 MPM_HD void stress_of(const float *G, const Material &mat, float tau[9], int &bad)
 {
     if (mat.model == 0) {
