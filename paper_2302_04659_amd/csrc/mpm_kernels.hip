@@ -596,7 +596,7 @@ __device__ __forceinline__ void load_row(float (&r)[N], const float *src)
 // k_gather for a state handed in as rows: each particle goes straight to its
 // sorted slot, its 24 floats in 5 or 6 cache lines where the gather from
 // component arrays in creation order takes 25 (7.7 million particles: in and
-// gather 460 + 995 -> 537 us).
+// gather 460 + 995 -> 550 us).
 __global__ __launch_bounds__(WG) void k_gather_rows(SortArgs a, StateRows w, int *flags)
 {
     const int p = xcd_remap(blockIdx.x, gridDim.x) * WG + threadIdx.x;
@@ -1903,7 +1903,7 @@ __device__ __forceinline__ void store_row(float *dst, const float (&r)[N])
 // part of a cache line, so a contiguous share of the slots per XCD keeps a
 // scene's lines in one L2 until its other particles have filled them, and all
 // loads come before the stores, which the compiler cannot tell apart from them
-// (7.7 million particles: 2010 -> 810 us, at a copy's rate 290; taking the caller's
+// (7.7 million particles: 2010 -> 740 us, at a copy's rate 290; taking the caller's
 // arrays directly saves 890 us of copies more).
 __global__ __launch_bounds__(WG) void k_get_state(const SceneDev *scenes, const int *psc, const float *P, long long ps,
                                                   int begin, int end, float *x, float *v, float *C, float *F)
