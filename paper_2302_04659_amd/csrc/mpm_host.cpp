@@ -107,6 +107,7 @@ struct mpm_ctx_s {
 
     // library-owned surrogate (mpm_surrogate_load / mpm_step_blocks): network and per-block arrays
     mpm::SurNet *net = nullptr;
+    bool dense = false;              // a scene with over 12 particles a cell at rest (see cut_of)
     bool whole_items = false;        // blocks cut to MPM_OPT_CHUNK only (see whole_items_from_now)
     int *d_sb_box = nullptr, *d_sb_origin = nullptr;
     float *d_sb_feat = nullptr, *d_sb_grid0 = nullptr, *d_sb_pred = nullptr, *d_sb_res = nullptr;
@@ -356,10 +357,17 @@ hipError_t resolve_timing(mpm_ctx ctx)
 // as long as the longest item, and the tile each further item stages and flushes
 // runs on idle CUs (65,536 particles, 25 substeps alone: 0.75 -> 0.60 ms; two
 // items per CU 0.66, one per two CUs 0.69).
+// Not where a scene's material holds over 12 particles a cell at rest: there the
+// node sum of the fullest cell sets the P2G's fixed-point scale, a piece holds
+// fewer of that cell's particles and gets a finer scale than its block, and the
+// results follow the launch configuration (20,000 fluid particles at 124 a cell:
+// velocity gradients 2e-4 away from whole blocks', 2.96 instead of 20.2 ms).  Up
+// to there the limit of the single term sets it nearly always: 20 particles in
+// the fullest cell of a scene at 8.
 int cut_of(mpm_ctx ctx)
 {
     if (ctx->persistent) return ctx->CH;   // its grid barriers cost per workgroup
-    if (ctx->whole_items) return ctx->CH;
+    if (ctx->whole_items || ctx->dense) return ctx->CH;
     const long long per_cu = ((long long)ctx->N + ctx->cus - 1) / ctx->cus;
     return (int)std::min<long long>(ctx->CH, std::max<long long>((per_cu + 63) / 64 * 64, 64));
 }
@@ -681,6 +689,7 @@ mpm_status create_impl(mpm_ctx ctx, const mpm_scene_desc *scenes, int n_scenes)
     for (int s = 0; s < n_scenes; s++) {
         const mpm_scene_desc &d = scenes[s];
         ctx->h_scenes.push_back(make_scene(d, p, (int)ctx->h_cols.size(), 4));
+        ctx->dense |= d.n_particles > 0 && (double)d.dx * d.dx * d.dx > 12.0 * d.particle_volume;
         for (int k = 0; k < d.n_colliders; k++) {
             const mpm_collider_shape &c = d.colliders[k];
             ColliderDev cd{};

@@ -163,15 +163,14 @@ __global__ __launch_bounds__(WG) void k_dilate(SortArgs a)
 static constexpr int SCAN_PER = 8;
 static constexpr int SCAN_TILE = WG * SCAN_PER;
 
-// Particles per item of a block with c of them: a.cut, or a.CH where the block
-// holds over 12 particles a cell.  An item's P2G takes its fixed-point scale from
-// its own scatter bound and fullest cell, so a piece has a finer scale than its
-// block, and the rounding of its terms follows the launch configuration.  In
-// dense material that shows (6,000 fluid particles at 40 a cell: velocity
-// gradients moved by 2e-5, 6,360 -> 3,160 us); where the single term's limit sets
-// the scale (up to about 20 particles in the fullest cell) it is the last bit of
-// the block's largest term.  The mean is a heuristic for that: a half-filled block
-// of dense material is below the line and is cut.
+// Particles per item of a block with c of them: a.cut (a.CH where the scenes'
+// material is dense at rest), or a.CH where the block holds over 12 particles a
+// cell all the same, compressed or placed on top of each other.  An item's P2G
+// takes its fixed-point scale from its own scatter bound and fullest cell, so in
+// dense material a piece has a finer scale than its block, and the rounding of
+// its terms would follow the launch configuration (6,000 fluid particles at 40 a
+// cell: velocity gradients moved by 2e-5, 6,360 -> 3,160 us).  Where the single
+// term's limit sets the scale it is the last bit of the block's largest term.
 __device__ __forceinline__ int item_size(const SortArgs &a, int c)
 {
     return c <= 12 * a.B * a.B * a.B ? a.cut : a.CH;
