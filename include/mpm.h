@@ -182,16 +182,17 @@ mpm_status mpm_get_particles(mpm_ctx ctx, int scene, float *x, float *v, float *
  * coordinates in the library's internal order (sorted by grid block, not
  * creation order); scene s holds slots [slot_begin[s], slot_begin[s + 1])
  * when slot_begin (host, n_scenes + 1 ints) is not NULL.  Read-only, and
- * valid only until the next call that steps or changes the state (mpm_step,
- * mpm_sur_block, mpm_set_state, mpm_autotune): a re-sort moves the
- * particles to the other buffer.  Synchronise the context stream before
+ * valid only until the next call that steps, sorts or changes the state
+ * (mpm_step, mpm_step_blocks, mpm_sur_features, mpm_sur_block, mpm_set_state,
+ * mpm_autotune): a re-sort moves the particles to the other buffer.  Synchronise the context stream before
  * reading. */
 mpm_status mpm_particle_view(mpm_ctx ctx, const float **x, const float **y, const float **z, int *slot_begin);
 
 /* Full particle state (checkpoint / teacher forcing): x, v [n][3]; affine
  * velocity C and deformation gradient F [n][3][3] of one scene or all
  * (scene = -1).  mpm_set_state replaces that state (all four arrays are
- * required) and re-sorts the particles.  Host arrays with a non-finite x or
+ * required) and re-sorts the particles, all scenes' in the call itself, one
+ * scene's of several with the next step.  Host arrays with a non-finite x or
  * v are refused (MPM_ERR_ARG); any other non-finite value (device arrays,
  * C, F, or an F without a defined stress) is reported by the next
  * mpm_sync as MPM_ERR_NONFINITE. */
